@@ -788,47 +788,57 @@ LevelArgs level_args(const sbt_ctx &X, int v, int mode) {
   return a;
 }
 
-sbt_status launch_level(sbt_ctx &X, int v, int p, int mode, hipStream_t s) {
-  Pool &P = X.pools[v];
-  LevelArgs a = level_args(X, v, mode);
-  auto timed = [&](bool fast, auto &&launch) -> sbt_status {
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (X.profiling) {
-      HIPCHK(hipEventCreate(&e0));
-      HIPCHK(hipEventCreate(&e1));
-      HIPCHK(hipEventRecord(e0, s));
-    }
-    HIPCHK(launch());
-    if (X.profiling) {
-      HIPCHK(hipEventRecord(e1, s));
-      (fast ? X.ev_fast : X.ev_level).push_back({e0, e1});
-    }
-    return SBT_OK;
-  };
-  sbt_status st = SBT_OK;
-  if (mode == 0) {
-    LevelArgs t = a;
+// One launch with the profiler's events around it.
+template <class F>
+sbt_status timed_launch(sbt_ctx &X, bool fast, hipStream_t s, F &&launch) {
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (X.profiling) {
+    HIPCHK(hipEventCreate(&e0));
+    HIPCHK(hipEventCreate(&e1));
+    HIPCHK(hipEventRecord(e0, s));
+  }
+  HIPCHK(launch());
+  if (X.profiling) {
+    HIPCHK(hipEventRecord(e1, s));
+    (fast ? X.ev_fast : X.ev_level).push_back({e0, e1});
+  }
+  return SBT_OK;
+}
+
+// The level substeps ph[0 .. n) (finest first, each one level coarser than
+// the one before) as one launch; see level_tile_kernel for why they do not
+// depend on each other.
+sbt_status launch_substeps(sbt_ctx &X, const Phase *ph, int n, hipStream_t s) {
+  LevelArgs lv[kMaxLevels];
+  bool any = false;
+  for (int i = 0; i < n; ++i) {
+    Pool &P = X.pools[ph[i].v];
+    LevelArgs &t = lv[i] = level_args(X, ph[i].v, 0);
     t.list = P.d_list;
     t.n_fast = (int)P.fast.size();
     t.n_blocks = (int)(P.fast.size() + P.slow.size());
-    t.kpw = blocks_per_wg(X, v, t.n_fast);
-    if (p == 1) {
+    t.kpw = blocks_per_wg(X, ph[i].v, t.n_fast);
+    t.solid = P.d_solid;
+    t.n_solid = (int)P.solid.size();
+    if (ph[i].p == 1) {
       t.band = P.d_band;
       t.n_band = (int)P.band.size();
     }
-    if (t.n_blocks + t.n_band > 0) st = timed(true, [&] { return sbt_launch_level_tile(X.kvar, &t, s); });
-    if (!st && !P.solid.empty()) {  // blocks next to solid cells: generic kernel, same substep
-      LevelArgs u = a;
-      u.list = P.d_solid;
-      u.n_blocks = (int)P.solid.size();
-      st = timed(false, [&] { return sbt_launch_level(X.kvar, 0, &u, s); });
-    }
-  } else {
-    a.list = nullptr;
-    a.b0 = 0;
-    a.n_blocks = P.n_own;
-    st = timed(false, [&] { return sbt_launch_level(X.kvar, 0, &a, s); });
+    any |= t.n_blocks + t.n_solid + t.n_band > 0;
+    P.cur = 1 - P.cur;
   }
+  return any ? timed_launch(X, true, s, [&] { return sbt_launch_level_tile(X.kvar, lv, n, s); }) : SBT_OK;
+}
+
+// Every owned block of pool v through the generic kernel (the first
+// collision of the initial state).
+sbt_status launch_level(sbt_ctx &X, int v, int mode, hipStream_t s) {
+  Pool &P = X.pools[v];
+  LevelArgs a = level_args(X, v, mode);
+  a.list = nullptr;
+  a.b0 = 0;
+  a.n_blocks = P.n_own;
+  sbt_status st = timed_launch(X, false, s, [&] { return sbt_launch_level(X.kvar, 0, &a, s); });
   if (st) return st;
   P.cur = 1 - P.cur;
   return SBT_OK;
@@ -909,7 +919,7 @@ sbt_status run_prologue(sbt_ctx &X, hipStream_t s) {
       if (!st) st = launch_mdf(X, true, s);
       if (st) return st;
     }
-    st = launch_level(X, v, 1, MODE_LOCAL, s);
+    st = launch_level(X, v, MODE_LOCAL, s);
     if (st) return st;
   }
   X.post = true;
@@ -921,11 +931,20 @@ sbt_status run_prologue(sbt_ctx &X, hipStream_t s) {
 sbt_status run_step_eager(sbt_ctx &X, hipStream_t s) {
   sbt_status st = launch_prep(X, forcing_phases(X), s);
   if (st) return st;
-  for (const Phase &ph : X.step_phases) {
-    st = ph.type == PH_MDF ? launch_mdf(X, false, s) : launch_level(X, ph.v, ph.p, 0, s);
-    if (st) return st;
+  const std::vector<Phase> &ph = X.step_phases;
+  for (size_t i = 0; i < ph.size() && !st;) {
+    if (ph[i].type == PH_MDF) {
+      st = launch_mdf(X, false, s);
+      ++i;
+      continue;
+    }
+    // a substep and the coarser levels' substeps that follow it directly
+    size_t n = 1;
+    while (i + n < ph.size() && ph[i + n].type == PH_LEVEL && ph[i + n].v == ph[i + n - 1].v - 1) ++n;
+    st = launch_substeps(X, &ph[i], (int)n, s);
+    i += n;
   }
-  return SBT_OK;
+  return st;
 }
 
 void destroy_graphs(sbt_ctx &X) {

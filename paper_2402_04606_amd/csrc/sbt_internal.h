@@ -1,6 +1,7 @@
 // Internal structures shared by the host engine and the gfx950 kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "sbt.h"
@@ -117,12 +118,31 @@ struct LevelArgs {
   int32_t ibm_parity;          // IBM plan buffer of the substep (-1: from the forcing-loop counter)
   const int32_t *band;         // halo-band cells (block * 256 + cell), gathered after the blocks
   int32_t n_band;
+  const int32_t *solid;        // tile launch: blocks with solid cells or links into them
+  int32_t n_solid;
   int32_t mode;                // MODE_* bits
   int32_t xcd_remap;
   double *out;                 // readout: [block - b0][3][256] rho, ux, uy
   double *partial;             // readout: [block - b0][3] mass, jx, jy partial sums
   int32_t *err;                // device error flags
 };
+
+// Arguments of a tile launch: the level substeps it runs, finest first, and
+// its work items.  Entry e covers `n` workgroups of one role of one substep.
+// The counts of the first 7 entries share 16 words with the header, so that
+// one scalar load serves most workgroups.
+enum : int32_t { ROLE_RUN = 0, ROLE_SLOW = 1, ROLE_BAND = 2, ROLE_SOLID = 3 };
+constexpr int kTileEntries = 4 * kMaxLevels;
+struct TileEntry {
+  int32_t n, what;             // workgroups; substep << 2 | role
+};
+struct alignas(64) TileArgs {
+  int32_t n_ent;
+  int32_t xcd_remap;
+  TileEntry ent[kTileEntries];
+  LevelArgs lv[kMaxLevels];
+};
+static_assert(offsetof(TileArgs, ent) == 8, "the header and 7 entries fill 16 words");
 
 struct MdfArgs {
   const BlockMeta *meta;       // finest pool
@@ -182,11 +202,13 @@ sbt_status sbt_set_error(sbt_status code, const char *msg);
 // initial collision) and halo-band cells.
 // `storage` of the level launches: SBT_F64 .. SBT_BF16S, plus 4 for the MRT collision.
 hipError_t sbt_launch_level(int storage, int tile, const sbt::LevelArgs *a, hipStream_t s);
-// One LDS-staged stream + collide launch for a level substep: list entries
-// [0, n_fast) are interior blocks (no cell codes, no domain edge, all eight
-// neighbours present), kpw of them per workgroup; [n_fast, n_blocks) blocks
-// next to a finer level or a domain edge; then n_band packed halo-band cells.
-hipError_t sbt_launch_level_tile(int storage, const sbt::LevelArgs *a, hipStream_t s);
+// One LDS-staged stream + collide launch of n level substeps that do not
+// depend on each other (finest first).  Of each: list entries [0, n_fast)
+// are interior blocks (no cell codes, no domain edge, all eight neighbours
+// present), kpw of them per workgroup; [n_fast, n_blocks) blocks next to a
+// finer level or a domain edge; then n_solid blocks with solid cells and
+// n_band packed halo-band cells.
+hipError_t sbt_launch_level_tile(int storage, const sbt::LevelArgs *a, int n, hipStream_t s);
 // One step as a single persistent launch of `groups` 1024-lane workgroups
 // (all resident at once) over the phase table `ph` (n_ph entries, device
 // memory), phases separated by grid barriers on bar[3] (zero between

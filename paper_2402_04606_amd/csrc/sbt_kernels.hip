@@ -17,6 +17,7 @@
 // [block][q][256] in the storage type, two lattices (read / write).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "sbt_internal.h"
 
@@ -92,19 +93,22 @@ struct Blk {
   int c0, c1, c2, c3;
 };
 
-__device__ __forceinline__ Blk load_blk(const BlockMeta *meta, int b) {
+// From the block table in global memory (P = const BlockMeta *) or through
+// the constant address space (scalar loads; the tables never change).
+template <class P>
+__device__ __forceinline__ Blk load_blk(P meta, int b) {
   Blk k;
-  const BlockMeta &m = meta[b];
+  const P m = meta + b;
   k.self = b;
-  k.ox = m.ox;
-  k.oy = m.oy;
-  k.level = m.level;
-  k.flags = m.flags;
-  k.code = m.code;
-  k.cid = m.case_id;
-  k.nE = m.nbr[0]; k.nN = m.nbr[1]; k.nW = m.nbr[2]; k.nS = m.nbr[3];
-  k.nNE = m.nbr[4]; k.nNW = m.nbr[5]; k.nSW = m.nbr[6]; k.nSE = m.nbr[7];
-  k.c0 = m.child[0]; k.c1 = m.child[1]; k.c2 = m.child[2]; k.c3 = m.child[3];
+  k.ox = m->ox;
+  k.oy = m->oy;
+  k.level = m->level;
+  k.flags = m->flags;
+  k.code = m->code;
+  k.cid = m->case_id;
+  k.nE = m->nbr[0]; k.nN = m->nbr[1]; k.nW = m->nbr[2]; k.nS = m->nbr[3];
+  k.nNE = m->nbr[4]; k.nNW = m->nbr[5]; k.nSW = m->nbr[6]; k.nSE = m->nbr[7];
+  k.c0 = m->child[0]; k.c1 = m->child[1]; k.c2 = m->child[2]; k.c3 = m->child[3];
   return k;
 }
 
@@ -797,33 +801,71 @@ __device__ __forceinline__ int remap_block(int bid, int nblk, int enable) {
   return start + k;
 }
 
-// Work item of tile-launch workgroup `bid` (roles: 0 interior run, 1 edge or
-// interface block, 2 band-cell group, -1 none).  Workgroups go to the 8
-// XCDs round-robin; XCD x takes the x-th eighth of each role (contiguous in
-// Morton order, so its halo reads stay in its own L2), band groups and
-// edge/interface blocks first: they are latency-bound and slower, so they
+typedef __attribute__((address_space(4))) const TileArgs ctile_t;
+typedef __attribute__((address_space(4))) const LevelArgs clevel_t;
+typedef __attribute__((address_space(4))) const BlockMeta cmeta_t;
+
+// Work item of tile-launch workgroup `bid`: its role, its substep and its
+// index within them (role -1: none).  Workgroups go to the 8 XCDs
+// round-robin; XCD x takes the x-th eighth of each entry (contiguous in
+// Morton order, so its halo reads stay in its own L2), the latency-bound
+// roles of every substep before the interior runs: they are slower, so they
 // are spread over all XCDs and overlap the streaming runs instead of
-// trailing at the end.  Without the remap the grid is plain
-// [runs | blocks | band groups].
-__device__ __forceinline__ int tile_role(int bid, int n_run, int n_blk, int n_bnd, int enable, int &idx) {
-  if (!enable) {
-    if (bid < n_run) { idx = bid; return 0; }
-    bid -= n_run;
-    if (bid < n_blk) { idx = bid; return 1; }
-    bid -= n_blk;
-    idx = bid;
-    return bid < n_bnd ? 2 : -1;
+// trailing at the end.  Without the remap the grid is the entries in order.
+typedef int int16_v __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ int tile_role(ctile_t *t, int bid, int &seg, int &idx) {
+  const int16_v h = *(__attribute__((address_space(4))) const int16_v *)t;
+  const int n_ent = h[0], remap = h[1];
+  const int x = remap ? bid & 7 : 0, sh = remap ? 3 : 0;
+  int k = bid >> sh;
+  // entry of n workgroups: this XCD's share of it, counted off from k
+  auto takes = [&](int n, int what) -> bool {
+    const int lo = n * x >> sh, c = (n * (x + 1) >> sh) - lo;
+    idx = lo + k;
+    seg = what >> 2;
+    k -= c;
+    return k < 0;
+  };
+#pragma unroll
+  for (int e = 0; e < 7; ++e)
+    if (takes(h[2 + 2 * e], h[3 + 2 * e])) return h[3 + 2 * e] & 3;  // entries past the last are empty
+  for (int e = 7; e < n_ent; ++e) {
+    const int what = t->ent[e].what;
+    if (takes(t->ent[e].n, what)) return what & 3;
   }
-  const int x = bid & 7, k = bid >> 3;
-  const int b0 = n_bnd * x / 8, b1 = n_bnd * (x + 1) / 8;
-  if (k < b1 - b0) { idx = b0 + k; return 2; }
-  const int k1 = k - (b1 - b0);
-  const int s0 = n_blk * x / 8, s1 = n_blk * (x + 1) / 8;
-  if (k1 < s1 - s0) { idx = s0 + k1; return 1; }
-  const int k2 = k1 - (s1 - s0);
-  const int r0 = n_run * x / 8, r1 = n_run * (x + 1) / 8;
-  if (k2 < r1 - r0) { idx = r0 + k2; return 0; }
   return -1;
+}
+
+// A pointer of the launch arguments as a global one: read through the
+// constant address space at a substep index known only at run time, its
+// address space would be lost, and flat accesses wait for the direct
+// copies into LDS.
+template <class T>
+__device__ __forceinline__ T *global_arg(__attribute__((address_space(4))) const void *field) {
+  const uint64_t v = *(__attribute__((address_space(4))) const uint64_t *)field;
+  return (T *)(__attribute__((address_space(1))) T *)v;
+}
+
+__device__ __forceinline__ LevelArgs load_level(clevel_t *p) {
+  LevelArgs a;
+  a.meta = global_arg<const BlockMeta>(&p->meta);
+  a.codes = global_arg<const uint16_t>(&p->codes);
+  a.src = global_arg<const char>(&p->src);
+  a.dst = global_arg<char>(&p->dst);
+  a.fmeta = global_arg<const BlockMeta>(&p->fmeta);
+  a.sbits = global_arg<const uint16_t>(&p->sbits);
+  a.sq = global_arg<const double>(&p->sq);
+  a.fprev = global_arg<const char>(&p->fprev);
+  a.fcur = global_arg<char>(&p->fcur);
+  a.n_blocks = p->n_blocks;
+  a.n_fast = p->n_fast;
+  a.kpw = p->kpw;
+  a.ibm_parity = p->ibm_parity;
+  a.band = global_arg<const int32_t>(&p->band);
+  a.n_band = p->n_band;
+  a.mode = 0;
+  a.err = global_arg<int32_t>(&p->err);
+  return a;
 }
 
 // Halo-band cell of a halo block: streamed in the first fine substep, never
@@ -1221,7 +1263,7 @@ __device__ __forceinline__ void ibm_force_of(const LevelArgs &a, const CaseDev *
 // waits for them before the barrier of the next step.
 template <int ST>
 __device__ __forceinline__ void pipe_step(const LevelArgs &a, const CaseDev *__restrict__ cases,
-                                          const BlockMeta *__restrict__ meta, Blk &kc, Blk &kn, int lv, int j, int cnt,
+                                          cmeta_t *meta, Blk &kc, Blk &kn, int lv, int j, int cnt,
                                           typename Store<ST>::T *cur, typename Store<ST>::T *nxt,
                                           typename Store<ST>::T &h, uint32_t he) {
   // after the first block, the previous block's 9 stores were issued after
@@ -1235,32 +1277,45 @@ __device__ __forceinline__ void pipe_step(const LevelArgs &a, const CaseDev *__r
   if (j + 2 < cnt) kn = load_blk(meta, __builtin_amdgcn_readlane(lv, j + 2));
 }
 
-// One launch per level substep.  With NBUF = 2, workgroups [0, n_fast_wg)
+// One launch for one or more level substeps that do not depend on each
+// other: a substep of level l streams from lattices that the second substep
+// of level l + 1 before it only reads (its own previous lattice, and for the
+// coalescence the one that substep streams from), and what it explodes goes
+// into halo blocks, which that substep does not write; so the substeps
+// between two forcing loops share a launch: 2^(V-1) of them a step instead
+// of 2^V - 1.  What bounds the short ones is launch and memory latency, not
+// bytes: a wing on 4 levels takes 8 launches of 4.8 to 7 us (43 us a step)
+// where it took 15 of 5.4 us (81 us); a 3-level cavity with solid cells 33 us
+// a step where it took 70 us, its solid blocks' own launches included.
+// With NBUF = 2, the workgroups of ROLE_RUN
 // each take a run of up to `kpw` consecutive interior blocks (no cell
 // codes, no domain edge, all eight neighbours) and copy block j+1 into the
-// second LDS image while block j is computed from the first.  The next
-// n_blocks - n_fast workgroups take one block next to a finer level or a
-// domain edge each; the rest gather packed halo-band cells.
-template <int ST, int NBUF>
-__global__ __launch_bounds__(256) void level_tile_kernel(LevelArgs a, const CaseDev *__restrict__ cases,
-                                                        const BlockMeta *__restrict__ meta, const int32_t *__restrict__ list) {
+// second LDS image while block j is computed from the first.  ROLE_SLOW
+// workgroups take one block next to a finer level or a domain edge each,
+// ROLE_SOLID (only with SOLID) one with solid cells through the per-cell
+// path; ROLE_BAND gather packed halo-band cells.
+template <int ST, int NBUF, bool SOLID>
+__global__ __launch_bounds__(256) void level_tile_kernel(TileArgs, const CaseDev *__restrict__ cases) {
   using T = typename Store<ST>::T;
   using TL = Tile<ST>;
   __shared__ __attribute__((aligned(16))) T bufA[TL::SIZE];
   __shared__ __attribute__((aligned(16))) T bufB[NBUF == 2 ? TL::SIZE : 8];
-  const int kpw = NBUF == 2 ? a.kpw : 1;
-  const int n_fast_wg = (a.n_fast + kpw - 1) / kpw;
-  const int n_band_wg = (a.n_band + 255) / 256;
-  int w0;
-  const int role = __builtin_amdgcn_readfirstlane(
-      tile_role(blockIdx.x, n_fast_wg, a.n_blocks - a.n_fast, n_band_wg, a.xcd_remap, w0));
+  ctile_t *args = (ctile_t *)__builtin_amdgcn_kernarg_segment_ptr();
+  int seg0 = 0, w0 = 0;
+  const int role = __builtin_amdgcn_readfirstlane(tile_role(args, blockIdx.x, seg0, w0));
+  if (role < 0) return;
   const int w = __builtin_amdgcn_readfirstlane(w0);  // wave-uniform: keeps block metadata on the scalar path
+  clevel_t *lev = args->lv + __builtin_amdgcn_readfirstlane(seg0);
+  const LevelArgs a = load_level(lev);
+  cmeta_t *meta = (cmeta_t *)a.meta;
+  ci32_t *list = (ci32_t *)global_arg<const int32_t>(&lev->list);
   const int lane = threadIdx.x & 63;
   // this lane's halo slot (neighbour code, element), the same for every
   // block: loaded before any copy is in flight
   const uint32_t he = threadIdx.x < 188 ? kHalo.e[threadIdx.x] : 0u;
   T h;
-  if (role == 0) {
+  if (role == ROLE_RUN) {
+    const int kpw = NBUF == 2 ? a.kpw : 1;
     const int first = w * kpw;
     const int cnt = min(kpw, a.n_fast - first);
     if (NBUF == 1 || cnt == 1) {
@@ -1284,7 +1339,7 @@ __global__ __launch_bounds__(256) void level_tile_kernel(LevelArgs a, const Case
     }
     return;
   }
-  if (role == 1) {
+  if (role == ROLE_SLOW) {
     __shared__ int cn[36];  // the finer blocks' neighbour tables (coalescence)
     const Blk k = load_blk(meta, list[a.n_fast + w]);
     double fx, fy;
@@ -1301,9 +1356,13 @@ __global__ __launch_bounds__(256) void level_tile_kernel(LevelArgs a, const Case
     if (threadIdx.x < 36) cn[threadIdx.x] = cv;
     commit_tile<ST>(bufA, h);
     compute_block<ST, true>(a, cases, k, bufA, fx, fy, code, cn);
-  } else if (role == 2) {
+  } else if (role == ROLE_BAND) {
     int idx = w * 256 + threadIdx.x;
     if (idx < a.n_band) band_cell<ST>(a, a.band[idx]);
+  } else if constexpr (SOLID) {
+    ci32_t *solid = (ci32_t *)global_arg<const int32_t>(&lev->solid);
+    const Blk k = load_blk(meta, solid[w]);
+    level_cell<ST>(a, k, threadIdx.x, cases[k.cid], true, nullptr);
   }
 }
 
@@ -2233,26 +2292,50 @@ hipError_t launch_level_st(int tile, const LevelArgs *a, hipStream_t s) {
 }  // namespace
 
 #ifndef SBT_PERSISTENT_TU
-extern "C" hipError_t sbt_launch_level_tile(int storage, const LevelArgs *a, hipStream_t s) {
-  if (a->kpw < 1) return hipErrorInvalidValue;
-  const bool pipe = a->kpw > 1;
-  const int kpw = pipe ? a->kpw : 1;
-  const int n_run = (a->n_fast + kpw - 1) / kpw, n_blk = a->n_blocks - a->n_fast, n_bnd = (a->n_band + 255) / 256;
-  int groups = n_run + n_blk + n_bnd;
-  if (groups <= 0) return hipSuccess;
-  if (a->xcd_remap) {  // 8 x the largest per-XCD share (see tile_role)
-    int most = 0;
-    for (int x = 0; x < 8; ++x) {
-      int c = (n_run * (x + 1) / 8 - n_run * x / 8) + (n_blk * (x + 1) / 8 - n_blk * x / 8) +
-              (n_bnd * (x + 1) / 8 - n_bnd * x / 8);
-      most = c > most ? c : most;
-    }
-    groups = 8 * most;
+extern "C" hipError_t sbt_launch_level_tile(int storage, const LevelArgs *lv, int n, hipStream_t s) {
+  if (n < 1 || n > kMaxLevels) return hipErrorInvalidValue;
+  TileArgs t;
+  memset(&t, 0, sizeof(t));
+  t.xcd_remap = lv[0].xcd_remap;
+  bool pipe = false, solid = false;
+  for (int i = 0; i < n; ++i) {
+    if (lv[i].kpw < 1) return hipErrorInvalidValue;
+    t.lv[i] = lv[i];
+    pipe |= lv[i].kpw > 1;
+    solid |= lv[i].n_solid > 0;
   }
+  const int order[4] = {ROLE_BAND, ROLE_SOLID, ROLE_SLOW, ROLE_RUN};
+  for (int r : order)
+    for (int i = 0; i < n; ++i) {
+      const LevelArgs &a = t.lv[i];
+      const int c = r == ROLE_BAND   ? (a.n_band + 255) / 256
+                    : r == ROLE_SOLID ? a.n_solid
+                    : r == ROLE_SLOW  ? a.n_blocks - a.n_fast
+                                      : (a.n_fast + a.kpw - 1) / a.kpw;
+      if (c > 0) t.ent[t.n_ent++] = {c, i << 2 | r};
+    }
+  int groups = 0;
+  if (t.xcd_remap) {  // 8 x the largest per-XCD share (see tile_role)
+    for (int x = 0; x < 8; ++x) {
+      int c = 0;
+      for (int e = 0; e < t.n_ent; ++e) c += (t.ent[e].n * (x + 1) >> 3) - (t.ent[e].n * x >> 3);
+      groups = c * 8 > groups ? c * 8 : groups;
+    }
+  } else {
+    for (int e = 0; e < t.n_ent; ++e) groups += t.ent[e].n;
+  }
+  if (groups <= 0) return hipSuccess;
+  const CaseDev *cases = t.lv[0].cases;
   dim3 grid(groups);
-#define SBT_TILE_LAUNCH(S)                                                               \
-  if (pipe) hipLaunchKernelGGL((level_tile_kernel<S, 2>), grid, dim3(256), 0, s, *a, a->cases, a->meta, a->list); \
-  else hipLaunchKernelGGL((level_tile_kernel<S, 1>), grid, dim3(256), 0, s, *a, a->cases, a->meta, a->list);
+#define SBT_TILE_LAUNCH(S)                                                                                       \
+  if (solid) {                                                                                                   \
+    if (pipe) hipLaunchKernelGGL((level_tile_kernel<S, 2, true>), grid, dim3(256), 0, s, t, cases);              \
+    else hipLaunchKernelGGL((level_tile_kernel<S, 1, true>), grid, dim3(256), 0, s, t, cases);                   \
+  } else if (pipe) {                                                                                             \
+    hipLaunchKernelGGL((level_tile_kernel<S, 2, false>), grid, dim3(256), 0, s, t, cases);                       \
+  } else {                                                                                                       \
+    hipLaunchKernelGGL((level_tile_kernel<S, 1, false>), grid, dim3(256), 0, s, t, cases);                       \
+  }
   switch (storage) {
     case 0: SBT_TILE_LAUNCH(0); break;
     case 1: SBT_TILE_LAUNCH(1); break;
