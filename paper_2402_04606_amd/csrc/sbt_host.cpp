@@ -746,19 +746,21 @@ struct Timer {
   hipEvent_t a = nullptr, b = nullptr;
 };
 
-// Interior blocks per workgroup of a tile launch.  Automatic: for 2-byte
-// storage as many as keep about four workgroups per resident slot (256 CUs
-// x 8), up to 8, so small launches still fill the chip and large ones
-// pipeline their loads; one otherwise.
+// Interior blocks per workgroup of a tile launch.  Automatic: runs of two for
+// 2-byte storage where the level fills the chip's 2048 resident workgroups
+// (256 CUs x 8), one block otherwise.  A run copies its second block while it
+// computes the first; 2-byte blocks move too few bytes to cover that latency
+// one at a time, and longer runs lose more to the drain than they hide.
+// Measured, us a step with 1 / 2 / 4 / 8 blocks: 64-case batch F16S 668 / 581
+// / 585 / 607 and BF16S 694 / 597 / 600 / 621; 4096^2 F16S 162 / 120 / 121 /
+// 127; 1024^2 (4096 blocks) F16S 13.0 / 12.1 / 11.7 / 13.4.  Below 2048 blocks
+// a run only makes the launch's longest workgroup longer (9-case batch 204 /
+// 206 / 223 / 261), and 4- and 8-byte blocks fill the memory pipes one at a
+// time (4096^2 F32 215 / 225 / 234 / 247, F64 430 / 442 / 465 / 500).
 int blocks_per_wg(const sbt_ctx &X, int v, int n_fast) {
   int k = v < (int)X.kpw_level.size() ? X.kpw_level[v] : 0;
   if (k > 0) return k;
-  // 8- and 4-byte storage saturate HBM with one block per workgroup; the
-  // 2-byte forms move too few bytes per block to hide latency without runs
-  if (storage_bytes(X.storage) > 2) return 1;
-  k = 1;
-  while (k < 8 && (int64_t)n_fast >= (int64_t)k * 2 * 4 * 2048) k *= 2;
-  return k;
+  return storage_bytes(X.storage) == 2 && n_fast >= 2048 ? 2 : 1;
 }
 
 // Arguments of a level launch of pool v in the current state.
