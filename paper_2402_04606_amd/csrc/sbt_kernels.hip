@@ -813,8 +813,7 @@ typedef __attribute__((address_space(4))) const BlockMeta cmeta_t;
 // are spread over all XCDs and overlap the streaming runs instead of
 // trailing at the end.  Without the remap the grid is the entries in order.
 typedef int int16_v __attribute__((ext_vector_type(16)));
-__device__ __forceinline__ int tile_role(ctile_t *t, int bid, int &seg, int &idx) {
-  const int16_v h = *(__attribute__((address_space(4))) const int16_v *)t;
+__device__ __forceinline__ int tile_role(ctile_t *t, const int16_v h, int bid, int &seg, int &idx) {
   const int n_ent = h[0], remap = h[1];
   const int x = remap ? bid & 7 : 0, sh = remap ? 3 : 0;
   int k = bid >> sh;
@@ -841,30 +840,43 @@ __device__ __forceinline__ int tile_role(ctile_t *t, int bid, int &seg, int &idx
 // address space would be lost, and flat accesses wait for the direct
 // copies into LDS.
 template <class T>
-__device__ __forceinline__ T *global_arg(__attribute__((address_space(4))) const void *field) {
-  const uint64_t v = *(__attribute__((address_space(4))) const uint64_t *)field;
+__device__ __forceinline__ T *global_at(uint64_t v) {
   return (T *)(__attribute__((address_space(1))) T *)v;
 }
+__device__ __forceinline__ uint64_t bits_of(__attribute__((address_space(4))) const void *field) {
+  return *(__attribute__((address_space(4))) const uint64_t *)field;
+}
 
-__device__ __forceinline__ LevelArgs load_level(clevel_t *p) {
+// The arguments of a substep that its interior blocks use (addresses as bits).
+struct RunArgs {
+  uint64_t meta, list, src, dst, err;
+  int n_fast, parity;
+};
+
+__device__ __forceinline__ RunArgs load_run(clevel_t *p) {
+  return {bits_of(&p->meta), bits_of(&p->list), bits_of(&p->src), bits_of(&p->dst), bits_of(&p->err), p->n_fast,
+          p->ibm_parity};
+}
+
+__device__ __forceinline__ LevelArgs load_level(clevel_t *p, const RunArgs &r) {
   LevelArgs a;
-  a.meta = global_arg<const BlockMeta>(&p->meta);
-  a.codes = global_arg<const uint16_t>(&p->codes);
-  a.src = global_arg<const char>(&p->src);
-  a.dst = global_arg<char>(&p->dst);
-  a.fmeta = global_arg<const BlockMeta>(&p->fmeta);
-  a.sbits = global_arg<const uint16_t>(&p->sbits);
-  a.sq = global_arg<const double>(&p->sq);
-  a.fprev = global_arg<const char>(&p->fprev);
-  a.fcur = global_arg<char>(&p->fcur);
+  a.meta = global_at<const BlockMeta>(r.meta);
+  a.codes = global_at<const uint16_t>(bits_of(&p->codes));
+  a.src = global_at<const char>(r.src);
+  a.dst = global_at<char>(r.dst);
+  a.fmeta = global_at<const BlockMeta>(bits_of(&p->fmeta));
+  a.sbits = global_at<const uint16_t>(bits_of(&p->sbits));
+  a.sq = global_at<const double>(bits_of(&p->sq));
+  a.fprev = global_at<const char>(bits_of(&p->fprev));
+  a.fcur = global_at<char>(bits_of(&p->fcur));
   a.n_blocks = p->n_blocks;
-  a.n_fast = p->n_fast;
+  a.n_fast = r.n_fast;
   a.kpw = p->kpw;
-  a.ibm_parity = p->ibm_parity;
-  a.band = global_arg<const int32_t>(&p->band);
+  a.ibm_parity = r.parity;
+  a.band = global_at<const int32_t>(bits_of(&p->band));
   a.n_band = p->n_band;
   a.mode = 0;
-  a.err = global_arg<int32_t>(&p->err);
+  a.err = global_at<int32_t>(r.err);
   return a;
 }
 
@@ -1301,14 +1313,22 @@ __global__ __launch_bounds__(256) void level_tile_kernel(TileArgs, const CaseDev
   __shared__ __attribute__((aligned(16))) T bufA[TL::SIZE];
   __shared__ __attribute__((aligned(16))) T bufB[NBUF == 2 ? TL::SIZE : 8];
   ctile_t *args = (ctile_t *)__builtin_amdgcn_kernarg_segment_ptr();
+  // What an interior block of the first substep needs loads with the header:
+  // the empty asm takes both, so neither waits behind the choice of the work
+  // item.
+  int16_v hdr = *(__attribute__((address_space(4))) const int16_v *)args;
+  RunArgs r = load_run(args->lv);
+  asm volatile("" : "+s"(hdr), "+s"(r.meta), "+s"(r.list), "+s"(r.src), "+s"(r.dst), "+s"(r.err), "+s"(r.n_fast), "+s"(r.parity));
   int seg0 = 0, w0 = 0;
-  const int role = __builtin_amdgcn_readfirstlane(tile_role(args, blockIdx.x, seg0, w0));
+  const int role = __builtin_amdgcn_readfirstlane(tile_role(args, hdr, blockIdx.x, seg0, w0));
   if (role < 0) return;
   const int w = __builtin_amdgcn_readfirstlane(w0);  // wave-uniform: keeps block metadata on the scalar path
-  clevel_t *lev = args->lv + __builtin_amdgcn_readfirstlane(seg0);
-  const LevelArgs a = load_level(lev);
-  cmeta_t *meta = (cmeta_t *)a.meta;
-  ci32_t *list = (ci32_t *)global_arg<const int32_t>(&lev->list);
+  const int seg = __builtin_amdgcn_readfirstlane(seg0);
+  clevel_t *lev = args->lv + seg;
+  if (seg > 0) r = load_run(lev);
+  const LevelArgs a = load_level(lev, r);
+  cmeta_t *meta = (cmeta_t *)r.meta;
+  ci32_t *list = (ci32_t *)r.list;
   const int lane = threadIdx.x & 63;
   // this lane's halo slot (neighbour code, element), the same for every
   // block: loaded before any copy is in flight
@@ -1360,7 +1380,7 @@ __global__ __launch_bounds__(256) void level_tile_kernel(TileArgs, const CaseDev
     int idx = w * 256 + threadIdx.x;
     if (idx < a.n_band) band_cell<ST>(a, a.band[idx]);
   } else if constexpr (SOLID) {
-    ci32_t *solid = (ci32_t *)global_arg<const int32_t>(&lev->solid);
+    ci32_t *solid = (ci32_t *)bits_of(&lev->solid);
     const Blk k = load_blk(meta, solid[w]);
     level_cell<ST>(a, k, threadIdx.x, cases[k.cid], true, nullptr);
   }
