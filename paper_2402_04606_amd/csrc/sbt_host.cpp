@@ -298,10 +298,17 @@ struct sbt_ctx {
   size_t p_lds = 0;
   std::vector<int> kpw_level;   // interior blocks per workgroup per virtual level (0: automatic)
   int lds_window = 0;           // IBM window cells whose plan-builder counters fit in LDS
+  int lds_window_beside = 0;    // the same beside a forcing loop, where a workgroup has the CU to itself
   int cell_cap = 0;             // stencil cells per IBM plan (fits the forcing kernel's LDS)
   int plan_bufs = 1;            // IBM plan buffers per body: the finest substeps of a step
   int max_body_markers = 0;     // largest body set so far (LDS table stride)
   int64_t k_host = 0;           // finest substeps issued (every body's forcing-loop counter)
+  // IBM plans beside the forcing loops: every plan_chunk-th loop's launch
+  // builds plan_chunk plans ahead; 0 = none (no body moves, one plan buffer,
+  // or too many bodies to leave CUs idle: a launch of their own per step).
+  int plan_chunk = 0;
+  bool plan_moving = false;     // some body is not fixed
+  bool plans_ready = false;     // the plans the next step takes as given are built
 
   std::vector<Phase> step_phases;
   std::vector<hipGraphExec_t> graph;   // [level-0 parity + 2 * plan buffer + 2 * plan_bufs * size index]
@@ -826,7 +833,11 @@ sbt_status launch_substeps(sbt_ctx &X, const Phase *ph, int n, hipStream_t s) {
       t.band = P.d_band;
       t.n_band = (int)P.band.size();
     }
-    any |= t.n_blocks + t.n_solid + t.n_band > 0;
+    if (ph[i].v == X.V - 1 && X.n_bodies > 0) {  // follows the forcing loops of the substep
+      t.bodies = X.d_bodies;
+      t.n_sum = X.n_bodies;
+    }
+    any |= t.n_blocks + t.n_solid + t.n_band + t.n_sum > 0;
     P.cur = 1 - P.cur;
   }
   return any ? timed_launch(X, true, s, [&] { return sbt_launch_level_tile(X.kvar, lv, n, s); }) : SBT_OK;
@@ -862,9 +873,18 @@ MdfArgs mdf_args(const sbt_ctx &X, bool first) {
   return a;
 }
 
+IbmArgs prep_args(const sbt_ctx &X, int n_plans, int n_moving, bool fixed);
+
 sbt_status launch_mdf(sbt_ctx &X, bool first, hipStream_t s) {
   if (X.n_bodies == 0) return SBT_OK;
   MdfArgs a = mdf_args(X, first);
+  IbmArgs p = prep_args(X, 0, X.plan_chunk, false);
+  if (X.plan_chunk > 0 && X.k_host % X.plan_chunk == 0) {
+    p.n_plans = X.plan_chunk;
+    p.first = X.plan_bufs - X.plan_chunk;
+    p.beside = a.parity;
+    p.lds_window = X.lds_window_beside;
+  }
   ++X.k_host;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (X.profiling) {
@@ -872,7 +892,7 @@ sbt_status launch_mdf(sbt_ctx &X, bool first, hipStream_t s) {
     HIPCHK(hipEventCreate(&e1));
     HIPCHK(hipEventRecord(e0, s));
   }
-  HIPCHK(sbt_launch_mdf(X.storage, &a, X.n_bodies, s));
+  HIPCHK(sbt_launch_mdf(X.storage, &a, &p, X.n_bodies, s));
   if (X.profiling) {
     HIPCHK(hipEventRecord(e1, s));
     X.ev_mdf.push_back({e0, e1});
@@ -886,11 +906,12 @@ int forcing_phases(const sbt_ctx &X) {
   return n;
 }
 
-// Build the IBM plans of every body for the next n_plans finest
-// substeps (those of kcount .. kcount + n_plans - 1), one workgroup per body
-// and substep.  The plan of substep k goes to buffer k & (plan_bufs - 1);
-// every earlier reader of those buffers precedes this launch in stream order.
-IbmArgs prep_args(const sbt_ctx &X, int n_plans) {
+// Plans of the n_plans finest substeps from kcount on, one workgroup per
+// body and substep; bodies in motion get the first n_moving of them, fixed
+// ones all or none.  The plan of substep k goes to buffer
+// k & (plan_bufs - 1); every earlier reader of those buffers precedes the
+// launch in stream order.
+IbmArgs prep_args(const sbt_ctx &X, int n_plans, int n_moving, bool fixed) {
   IbmArgs a;
   a.cases = X.d_cases;
   a.bodies = X.d_bodies;
@@ -899,13 +920,36 @@ IbmArgs prep_args(const sbt_ctx &X, int n_plans) {
   a.lds_window = X.lds_window;
   a.n_bodies = X.n_bodies;
   a.n_plans = n_plans;
+  a.first = 0;
+  a.n_moving = n_moving;
+  a.fixed = fixed;
+  a.beside = -1;
   return a;
 }
 
+// Plans that stand before the next step's launches: a fixed body's in every
+// buffer (it serves every substep, so it is built once), a moving body's up
+// to where the launches beside the forcing loops take over.  With plan_chunk
+// c the loop of a substep k that c divides builds the plans of substeps
+// k + B - c .. k + B - 1 (B buffers); the substeps k - c .. k - 1 whose
+// buffers they take have collided.  Called before a step, never in a capture.
+sbt_status ensure_plans(sbt_ctx &X, hipStream_t s) {
+  if (X.n_bodies == 0 || X.plans_ready) return SBT_OK;
+  const int B = X.plan_bufs, c = X.plan_chunk;
+  const int n_moving = c > 0 ? (int)((X.k_host + c - 1) / c * c - X.k_host) + B - c : 0;
+  IbmArgs a = prep_args(X, B, n_moving, true);
+  a.lds_window = X.lds_window_beside;
+  HIPCHK(sbt_launch_ibm_prep(&a, s));
+  X.plans_ready = true;
+  return SBT_OK;
+}
+
+// The moving bodies' plans of the next n_plans finest substeps, where they
+// have a launch of their own.
 sbt_status launch_prep(sbt_ctx &X, int n_plans, hipStream_t s) {
-  if (X.n_bodies == 0) return SBT_OK;
+  if (X.n_bodies == 0 || !X.plan_moving || X.plan_chunk > 0) return SBT_OK;
   if (n_plans > X.plan_bufs) return fail(SBT_ERR_STATE, "more IBM plans than plan buffers");
-  IbmArgs a = prep_args(X, n_plans);
+  const IbmArgs a = prep_args(X, n_plans, n_plans, false);
   HIPCHK(sbt_launch_ibm_prep(&a, s));
   return SBT_OK;
 }
@@ -917,9 +961,11 @@ sbt_status run_prologue(sbt_ctx &X, hipStream_t s) {
   sbt_status st = SBT_OK;
   for (int v = X.V - 1; v >= 0; --v) {
     if (v == X.V - 1) {
-      st = launch_prep(X, 1, s);
+      st = ensure_plans(X, s);
+      if (!st) st = launch_prep(X, 1, s);
       if (!st) st = launch_mdf(X, true, s);
       if (st) return st;
+      HIPCHK(sbt_launch_body_force(X.d_bodies, X.n_bodies, s));
     }
     st = launch_level(X, v, MODE_LOCAL, s);
     if (st) return st;
@@ -928,8 +974,8 @@ sbt_status run_prologue(sbt_ctx &X, hipStream_t s) {
   return SBT_OK;
 }
 
-// One step: the IBM plans of all its finest substeps (they depend on the
-// marker positions only), then the phases in order.
+// One step: the IBM plans of its finest substeps that have a launch of their
+// own (they depend on the marker positions only), then the phases in order.
 sbt_status run_step_eager(sbt_ctx &X, hipStream_t s) {
   sbt_status st = launch_prep(X, forcing_phases(X), s);
   if (st) return st;
@@ -976,7 +1022,7 @@ void build_phase_table(sbt_ctx &X, std::vector<PPhase> &out) {
   if (X.n_bodies > 0) {
     PPhase q = blank();
     q.type = PP_PREP;
-    q.ibm = prep_args(X, forcing_phases(X));
+    q.ibm = prep_args(X, forcing_phases(X), forcing_phases(X), true);
     q.n_items = X.n_bodies * q.ibm.n_plans;
     out.push_back(q);
   }
@@ -1038,6 +1084,7 @@ sbt_status run_step_persistent(sbt_ctx &X, hipStream_t s) {
   }
   HIPCHK(sbt_launch_step_persistent(X.kvar, tab, X.ptab_n[slot], X.d_bar, X.d_err, X.p_spins, X.p_groups, X.p_lds, s));
   advance_host(X, 1);
+  X.plans_ready = false;  // the step built the plans of its own substeps only
   return SBT_OK;
 }
 
@@ -1190,6 +1237,7 @@ sbt_status reset_counters(sbt_ctx &X) {
   }
   X.post = false;
   X.k_host = 0;
+  X.plans_ready = false;
   for (auto &P : X.pools) P.cur = 0;
   destroy_graphs(X);
   return SBT_OK;
@@ -1462,6 +1510,7 @@ sbt_status sbt_set_body(sbt_ctx *ctx, int32_t c, const sbt_body *body) {
     const size_t half = (size_t)lds_max / 2 - 1024;
     const size_t budget = prep + 4096 * 4 <= half ? half : (size_t)lds_max - 1024;
     X.lds_window = (int)std::min<size_t>(32768, (budget - prep) / 4 - 1);
+    X.lds_window_beside = (int)std::min<size_t>(32768, ((size_t)lds_max - 1024 - prep) / 4 - 1);
     X.max_body_markers = nmax;
   }
   HIPCHK(hipStreamSynchronize(X.stream));
@@ -1481,6 +1530,19 @@ sbt_status sbt_set_body(sbt_ctx *ctx, int32_t c, const sbt_body *body) {
     if (K.has_body && K.n_markers > 0) bd.push_back(K.dev);
   X.n_bodies = (int)bd.size();
   if (!bd.empty()) HIPCHK(hipMemcpy(X.d_bodies, bd.data(), sizeof(CaseDev) * bd.size(), hipMemcpyHostToDevice));
+  // Plans beside the forcing loops, where both fit the 256 CUs (each takes a
+  // whole one): as many at a time as fit, up to half the buffers, since the
+  // builder is slower than the loop and makes its launch longer.  Markers
+  // placed by the caller change between steps: their plans are built then.
+  X.plan_moving = false;
+  bool placed = false;
+  for (const CaseDev &D : bd) {
+    X.plan_moving |= D.body_kind != SBT_BODY_FIXED;
+    placed |= D.body_kind == SBT_BODY_HOST;
+  }
+  X.plan_chunk = X.plan_moving && !placed ? X.plan_bufs / 2 : 0;
+  while (X.plan_chunk > 0 && X.n_bodies * (1 + X.plan_chunk) > 256) X.plan_chunk /= 2;
+  X.plans_ready = false;
   destroy_graphs(X);
   return SBT_OK;
 }
@@ -1514,6 +1576,10 @@ sbt_status sbt_step(sbt_ctx *ctx, int32_t n) {
   if (n == 0) return SBT_OK;
   if (!X.post) {
     sbt_status st = run_prologue(X, X.stream);
+    if (st) return st;
+  }
+  if (!X.persistent || X.profiling) {
+    sbt_status st = ensure_plans(X, X.stream);
     if (st) return st;
   }
   for (int t = 0; t < n;) {
@@ -1836,6 +1902,7 @@ sbt_status sbt_write_state(sbt_ctx *ctx, const void *host, size_t bytes) {
     p += nb;
   }
   X.post = h.post != 0;
+  X.plans_ready = false;
   for (size_t i = 0; i < X.pools.size(); ++i) X.pools[i].cur = curs[i];
   destroy_graphs(X);
   return SBT_OK;
@@ -1873,6 +1940,7 @@ sbt_status sbt_profile(sbt_ctx *ctx, int32_t n, double out[9]) {
   X.ev_mdf.clear();
   sbt_status st = SBT_OK;
   if (!X.post) st = run_prologue(X, X.stream);
+  if (!st) st = ensure_plans(X, X.stream);
   X.ev_level.clear();
   X.ev_fast.clear();
   X.ev_mdf.clear();

@@ -85,14 +85,15 @@ struct alignas(16) CaseDev {
   int32_t cell_cap;            // stencil-cell capacity of a plan
   int32_t plan_mask;           // plan buffers - 1 (a power of two >= the finest substeps of a step)
   IbmWindow *win;              // [plan_mask + 1] window of the plan in buffer k & plan_mask
-  int32_t *phdr;               // [plan_mask + 1][4] plan header: stamp (low 32 bits of k), stencil cells, status, 0
+  int32_t *phdr;               // [plan_mask + 1][4] plan header: stamp (low 32 bits of k), stencil cells, status,
+                               // 1 if the plan serves every substep (fixed body)
   double *wF;                  // [plan_mask + 1][2][win_cap] force density in the window, per plan buffer
   int32_t *wCnt, *wIdx;        // [plan_mask + 1][win_cap] plan builder's counters / compact index beyond LDS
-  int32_t *p_ij;               // [plan_mask + 1][2][nm_cap] first tap of each marker (x, y)
-  double *p_w;                 // [plan_mask + 1][8][nm_cap] Peskin weights of the 4 x and 4 y taps
+  int32_t *p_ij;               // [plan_mask + 1][2 nm_cap] first tap of each marker (x | y << 16; half of it used)
+  double *p_w;                 // [plan_mask + 1][nm_cap][8] Peskin weights of the 4 x and 4 y taps
   double *p_ud;                // [plan_mask + 1][2][nm_cap] desired marker velocity
-  uint16_t *p_tap;             // [plan_mask + 1][16][nm_cap] stencil cell of each tap
-  int32_t *p_cell;             // [plan_mask + 1][cell_cap][8] window index, 4 source blocks, list start, count, 0
+  uint16_t *p_tap;             // [plan_mask + 1][nm_cap][16] stencil cell of each tap
+  int32_t *p_cell;             // [plan_mask + 1][cell_cap][8] gather and spread records (PlanView)
   uint16_t *p_list;            // [plan_mask + 1][16 nm_cap] markers over each stencil cell, ascending
   const int32_t *bmap;         // finest-level block map -> pool index (-1 outside)
 };
@@ -120,6 +121,8 @@ struct LevelArgs {
   int32_t n_band;
   const int32_t *solid;        // tile launch: blocks with solid cells or links into them
   int32_t n_solid;
+  const CaseDev *bodies;       // tile launch: bodies whose force F_s of the substep it sums
+  int32_t n_sum;
   int32_t mode;                // MODE_* bits
   int32_t xcd_remap;
   double *out;                 // readout: [block - b0][3][256] rho, ux, uy
@@ -131,10 +134,10 @@ struct LevelArgs {
 // its work items.  Entry e covers `n` workgroups of one role of one substep.
 // The counts of the first 7 entries share 16 words with the header, so that
 // one scalar load serves most workgroups.
-enum : int32_t { ROLE_RUN = 0, ROLE_SLOW = 1, ROLE_BAND = 2, ROLE_SOLID = 3 };
-constexpr int kTileEntries = 4 * kMaxLevels;
+enum : int32_t { ROLE_RUN = 0, ROLE_SLOW = 1, ROLE_BAND = 2, ROLE_SOLID = 3, ROLE_SUM = 4 };
+constexpr int kTileEntries = 4 * kMaxLevels + 1;
 struct TileEntry {
-  int32_t n, what;             // workgroups; substep << 2 | role
+  int32_t n, what;             // workgroups; substep << 3 | role
 };
 struct alignas(64) TileArgs {
   int32_t n_ent;
@@ -163,7 +166,11 @@ struct IbmArgs {
   int32_t cell_cap;            // stencil-cell capacity
   int32_t lds_window;          // window cells whose counters fit in LDS
   int32_t n_bodies;            // bodies per plan: workgroup w builds plan w / n_bodies of body w % n_bodies
-  int32_t n_plans;             // plans per body: substeps kcount .. kcount + n_plans - 1
+  int32_t n_plans;             // plans per body: substeps kcount + first .. kcount + first + n_plans - 1
+  int32_t first;
+  int32_t n_moving;            // how many of those a body in motion gets
+  int32_t fixed;               // whether fixed bodies get theirs (one plan serves every substep)
+  int32_t beside;              // >= 0: launched with the forcing loop of the substep in this plan buffer
 };
 
 // One phase of the persistent step (one launch per step): the plan builder
@@ -221,8 +228,11 @@ hipError_t sbt_launch_step_persistent(int storage, const sbt::PPhase *ph, int n_
 int sbt_step_persistent_occupancy(int storage, size_t lds_bytes);
 // IBM plan of the next finest substep of every body, one workgroup each.
 hipError_t sbt_launch_ibm_prep(const sbt::IbmArgs *a, hipStream_t s);
-// Multi-direct forcing loop of the current finest substep on its plan.
-hipError_t sbt_launch_mdf(int storage, const sbt::MdfArgs *a, int n_bodies, hipStream_t s);
+// Multi-direct forcing loop of the current finest substep on its plan, and
+// beside it (p->n_plans > 0) the workgroups that build later substeps' plans.
+hipError_t sbt_launch_mdf(int storage, const sbt::MdfArgs *a, const sbt::IbmArgs *p, int n_bodies, hipStream_t s);
+// Body force F_s of the forcing loops just run, where no tile launch follows.
+hipError_t sbt_launch_body_force(const sbt::CaseDev *bodies, int n_bodies, hipStream_t s);
 size_t sbt_mdf_lds_bytes(int max_markers, int cell_cap);
 size_t sbt_prep_lds_bytes(int max_markers, int cell_cap, int lds_window);
 hipError_t sbt_launch_reduce(const double *partial, int n_blocks, double vol, double *out,

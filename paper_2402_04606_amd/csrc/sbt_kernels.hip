@@ -821,16 +821,16 @@ __device__ __forceinline__ int tile_role(ctile_t *t, const int16_v h, int bid, i
   auto takes = [&](int n, int what) -> bool {
     const int lo = n * x >> sh, c = (n * (x + 1) >> sh) - lo;
     idx = lo + k;
-    seg = what >> 2;
+    seg = what >> 3;
     k -= c;
     return k < 0;
   };
 #pragma unroll
   for (int e = 0; e < 7; ++e)
-    if (takes(h[2 + 2 * e], h[3 + 2 * e])) return h[3 + 2 * e] & 3;  // entries past the last are empty
+    if (takes(h[2 + 2 * e], h[3 + 2 * e])) return h[3 + 2 * e] & 7;  // entries past the last are empty
   for (int e = 7; e < n_ent; ++e) {
     const int what = t->ent[e].what;
-    if (takes(t->ent[e].n, what)) return what & 3;
+    if (takes(t->ent[e].n, what)) return what & 7;
   }
   return -1;
 }
@@ -1289,6 +1289,49 @@ __device__ __forceinline__ void pipe_step(const LevelArgs &a, const CaseDev *__r
   if (j + 2 < cnt) kn = load_blk(meta, __builtin_amdgcn_readlane(lv, j + 2));
 }
 
+// Body force of Eq. (16), F_s = -sum_j F_j ds_j in marker order, of the
+// forcing loop last run (256 threads; prod holds 256 products per component):
+// a serial chain of FP64 additions, x on one lane and y on the next, beside
+// the level launch that follows the loop (at the loop's end, where nothing
+// else ran beside it, it cost 1.3 us with 200 markers and 2.5 with 402).
+__device__ __forceinline__ void body_force(const CaseDev &cp, double *prod) {
+#pragma clang fp contract(off)
+  const int n = cp.n_markers, tid = threadIdx.x;
+  const int64_t k = *cp.kcount - 1;
+  const double *ft = cp.ftot + (size_t)(k & 1) * 2 * n, *ds = cp.ds;
+  double fs = 0.0;
+  for (int j0 = 0; j0 < n; j0 += 256) {
+    if (j0 + tid < n) {
+      const double d = ds[j0 + tid];
+      prod[2 * tid] = ft[j0 + tid] * d;
+      prod[2 * tid + 1] = ft[n + j0 + tid] * d;
+    }
+    __syncthreads();
+    if (tid < 2) {
+      const int m = min(256, n - j0);
+      const double *v = prod + tid;
+      int j = 0;
+      for (; j + 16 <= m; j += 16) {
+        double t[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t[r] = v[2 * (j + r)];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) fs -= t[r];
+      }
+      for (; j < m; ++j) fs -= v[2 * j];
+    }
+    __syncthreads();
+  }
+  if (tid < 2) cp.hist[2 * (k % cp.hist_cap) + tid] = fs;
+}
+
+#ifndef SBT_PERSISTENT_TU
+__global__ __launch_bounds__(256) void body_force_kernel(const CaseDev *bodies) {
+  __shared__ double prod[512];
+  body_force(bodies[blockIdx.x], prod);
+}
+#endif
+
 // One launch for one or more level substeps that do not depend on each
 // other: a substep of level l streams from lattices that the second substep
 // of level l + 1 before it only reads (its own previous lattice, and for the
@@ -1305,7 +1348,7 @@ __device__ __forceinline__ void pipe_step(const LevelArgs &a, const CaseDev *__r
 // second LDS image while block j is computed from the first.  ROLE_SLOW
 // workgroups take one block next to a finer level or a domain edge each,
 // ROLE_SOLID (only with SOLID) one with solid cells through the per-cell
-// path; ROLE_BAND gather packed halo-band cells.
+// path; ROLE_BAND gather packed halo-band cells; ROLE_SUM sum one body's F_s.
 template <int ST, int NBUF, bool SOLID>
 __global__ __launch_bounds__(256) void level_tile_kernel(TileArgs, const CaseDev *__restrict__ cases) {
   using T = typename Store<ST>::T;
@@ -1379,6 +1422,9 @@ __global__ __launch_bounds__(256) void level_tile_kernel(TileArgs, const CaseDev
   } else if (role == ROLE_BAND) {
     int idx = w * 256 + threadIdx.x;
     if (idx < a.n_band) band_cell<ST>(a, a.band[idx]);
+  } else if (role == ROLE_SUM) {
+    static_assert(sizeof(bufA) >= 512 * sizeof(double), "products of 256 markers");
+    body_force(global_at<const CaseDev>(bits_of(&lev->bodies))[w], reinterpret_cast<double *>(bufA));
   } else if constexpr (SOLID) {
     ci32_t *solid = (ci32_t *)bits_of(&lev->solid);
     const Blk k = load_blk(meta, solid[w]);
@@ -1387,21 +1433,23 @@ __global__ __launch_bounds__(256) void level_tile_kernel(TileArgs, const CaseDev
 }
 
 // ---- IBM: multi-direct forcing (Sec. 2.2), one workgroup per body ----------
-// Two kernels per finest substep k of every body:
-//  * ibm_prep_kernel builds the plan of substep k one substep ahead.  It
-//    needs only the prescribed kinematics and the block map: marker
-//    positions, desired velocities and Peskin weights (Eqs. (13), (14)), the
-//    IBM window, the compact list of stencil cells with the blocks their
-//    streaming sources lie in, and for every stencil cell the markers whose
-//    stencil covers it, in ascending marker index (CSR).
-//  * mdf_kernel runs the forcing loop of substep k on that plan: cell
-//    moments, N_F iterations of interpolation (Eq. (12)), boundary force
-//    (Eq. (11)) and spreading (Eq. (15)), with the moments and the marker
-//    tables in LDS and each stencil cell's force in its owner's registers,
-//    then the force density for the collision and the body force (Eq. (16)).
+// Of every body and finest substep k:
+//  * the plan (prep_item): it needs only the prescribed kinematics and the
+//    block map: marker positions, desired velocities and Peskin weights
+//    (Eqs. (13), (14)), the IBM window, the stencil cells with the blocks
+//    their streaming sources lie in, and for every stencil cell the markers
+//    whose stencil covers it, in ascending marker index (CSR).
+//  * the forcing loop (mdf_body) on that plan: cell moments, N_F iterations
+//    of interpolation (Eq. (12)), boundary force (Eq. (11)) and spreading
+//    (Eq. (15)), with the moments and the marker tables in LDS, then the
+//    force density for the collision and the total marker forces.
+//  * the body force (Eq. (16)), summed beside the level launch that follows.
 // Plans live in plan_mask + 1 buffers (index k & plan_mask), and so do the
-// window and its force density that the collision of substep k reads: one
-// launch builds the plans of all finest substeps of a coarse step.
+// window and its force density that the collision of substep k reads.  A
+// fixed body's plans are built once.  A moving body's are built ahead, by
+// workgroups beside the forcing loops on CUs these leave idle, where both
+// fit the chip, else by a launch of their own per step (ensure_plans and
+// launch_prep of the host).
 constexpr int MDF_THREADS = kMaxMarkers;
 
 __device__ __forceinline__ double peskin(double r) {
@@ -1467,38 +1515,28 @@ __device__ __forceinline__ double pitch_angle(const CaseDev &cp, double ts) {
   return q * r / (2.0 * ta3) * s * s * s * s + r / ta2 * s * s * s + (up ? a0 : -a0);
 }
 
-__device__ Pose body_pose(const CaseDev &cp, double k) {
+// One quantity of the pose at substep k (what: 0 x centre, 1 y centre, 2 cos,
+// 3 sin of the angle), so that lanes of different waves find them together.
+__device__ double body_pose(const CaseDev &cp, double k, int what) {
 #pragma clang fp contract(off)
   const double *p = cp.bp;
-  Pose r;
-  r.xc = p[0];
-  r.yc = p[1];
-  if (cp.body_kind == 0) {
-    r.ca = 1.0;
-    r.sa = 0.0;
-    return r;
-  }
+  if (cp.body_kind == 0) return what == 0 ? p[0] : (what == 1 ? p[1] : (what == 2 ? 1.0 : 0.0));
   const double tstar = k * p[8] / p[9];
-  const double alpha = pitch_angle(cp, tstar);
-  if (cp.body_kind == 1) {  // plunge along the stroke angle
-    const double h = 0.5 * p[4] * cos(2.0 * M_PI * tstar / p[6]);
-    r.xc = p[0] + h * cos(p[5]);
-    r.yc = p[1] + h * sin(p[5]);
+  if (what >= 2) {
+    const double alpha = pitch_angle(cp, tstar);
+    return what == 2 ? cos(alpha) : sin(alpha);
   }
-  r.ca = cos(alpha);
-  r.sa = sin(alpha);
-  return r;
+  if (cp.body_kind != 1) return p[what];
+  // plunge along the stroke angle
+  const double h = 0.5 * p[4] * cos(2.0 * M_PI * tstar / p[6]);
+  return p[what] + h * (what == 0 ? cos(p[5]) : sin(p[5]));
 }
 
-__device__ __forceinline__ void marker_position(const CaseDev &cp, const Pose &q, int j, double &X, double &Y) {
+// Coordinate `axis` of the marker at (xb, yb) of the body frame.
+__device__ __forceinline__ double marker_position(int kind, const Pose &q, double xb, double yb, int axis) {
 #pragma clang fp contract(off)
-  if (cp.body_kind == 0) {
-    X = q.xc + cp.xb[j];
-    Y = q.yc + cp.yb[j];
-    return;
-  }
-  X = q.xc + cp.xb[j] * q.ca + cp.yb[j] * q.sa;
-  Y = q.yc - cp.xb[j] * q.sa + cp.yb[j] * q.ca;
+  if (kind == 0) return axis == 0 ? q.xc + xb : q.yc + yb;
+  return axis == 0 ? q.xc + xb * q.ca + yb * q.sa : q.yc - xb * q.sa + yb * q.ca;
 }
 
 // Owned finest-level block of the case holding cell (gx, gy), -1 if none.
@@ -1534,20 +1572,20 @@ __device__ __forceinline__ void sort_net(int (&v)[N]) {
 
 // Plan buffer b of a case: element offsets of its arrays.
 struct PlanView {
-  int32_t *i0, *j0;      // first tap of each marker
-  double *w;             // [8][nm]: wx[0..3], wy[0..3]
+  int32_t *ij;           // [nm] first tap of each marker, x | y << 16
+  double *w;             // [nm][8]: wx[0..3], wy[0..3]
   double *ud;            // [2][nm]: desired velocity (x, y)
-  uint16_t *tap;         // [16][nm]: stencil cell of each tap (y outer, x inner)
-  int32_t *cell;         // [cell_cap][8]: window index, 4 source blocks, csr start, count, 0
+  uint16_t *tap;         // [nm][16]: stencil cell (place q) of each tap (y outer, x inner)
+  int32_t *cell;         // [cell_cap][8]: gather record of place g: 4 source blocks, x | y << 16, place q;
+                         //   spread record of place q: csr start | count << 16, x | y << 16
   uint16_t *list;        // [16 nm]: contributors of the stencil cells, CSR
-  int32_t *hdr;          // [4]: stamp (low 32 bits of k), stencil cells, status, 0
+  int32_t *hdr;          // [4]: stamp (low 32 bits of k), stencil cells, status, serves every substep
 };
 
 __device__ __forceinline__ PlanView plan_view(const CaseDev &cp, int b) {
   const size_t nm = (size_t)cp.nm_cap;
   PlanView v;
-  v.i0 = cp.p_ij + (size_t)b * 2 * nm;
-  v.j0 = v.i0 + nm;
+  v.ij = cp.p_ij + (size_t)b * 2 * nm;
   v.w = cp.p_w + (size_t)b * 8 * nm;
   v.ud = cp.p_ud + (size_t)b * 2 * nm;
   v.tap = cp.p_tap + (size_t)b * 16 * nm;
@@ -1557,16 +1595,40 @@ __device__ __forceinline__ PlanView plan_view(const CaseDev &cp, int b) {
   return v;
 }
 
+// Contributors of a stencil cell (n_c <= N of them) from its LDS list to the
+// plan's, in ascending marker order.
+template <int N>
+__device__ __forceinline__ void sort_out(const uint16_t *L, uint16_t *O, int n_c) {
+  int v[N];
+#pragma unroll
+  for (int r = 0; r < N; ++r) v[r] = r < n_c ? (int)L[r] : 0x7fffffff;
+  sort_net<N>(v);
+#pragma unroll
+  for (int r = 0; r < N; ++r)
+    if (r < n_c) O[r] = (uint16_t)v[r];
+}
+
 // Plan builder.  LDS: window counters and compact indices (when the window
 // fits), the stencil cells' window indices and CSR starts, the contributor
 // lists while they are filled.
 // Plan `item` of the launch: substep item / n_bodies of body item % n_bodies.
 // The arguments come by value, as a kernel's do: taken by reference they
 // cost the plan builder 4 more VGPRs (one builder per CU instead of two).
+// A copy of its own for each kernel (K): two kernels that share a function's
+// LDS variables address them through a table.
+// With PAIR two lanes share a marker (bodies of up to 512 markers): one axis
+// each for the position and weights, two rows of taps each.
+// A serial chain of phases bounds it (LDS atomics and a barrier each), so
+// the stencil cells are put in descending order of their contributor count
+// by a counting sort: within a count the lists have one length, which gives
+// their starts without a scan, and waves of cells with equal counts sort
+// here, and spread in the forcing loop, only as far as their own cells need.
+template <int K, bool PAIR>
 __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
 #pragma clang fp contract(off)
-  const int64_t j = item / a.n_bodies;  // plan of the launch's j-th substep
+  const int j = item / a.n_bodies;  // plan of the launch's j-th substep
   const CaseDev &cp = a.bodies[item % a.n_bodies];
+  if (cp.body_kind == 0 ? !a.fixed : j >= a.n_moving) return;
   const int n = cp.n_markers;
   const int nm = cp.nm_cap, cap = cp.cell_cap;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1579,71 +1641,100 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
   // their compact indices (16 bits)
   uint32_t *s_cnt = reinterpret_cast<uint32_t *>(s_list + 16 * NMa);  // [(lds_window + 1) / 2]
   uint16_t *s_idx = reinterpret_cast<uint16_t *>(s_cnt + (a.lds_window + 1) / 2);  // [lds_window]
-  __shared__ int s_box[4];
-  __shared__ int s_ns, s_bad;
+  // cells per contributor count (the last bin: that many or more), then the
+  // first cell and list start of each; s_over: list space of the last bin
+  constexpr int kBins = 64;
+  __shared__ int s_bin[kBins], s_binq[kBins], s_binc[kBins], s_over;
   __shared__ int s_wsum[MDF_THREADS / 64];
-  __shared__ Pose s_pose[2];
-  // the forcing loop of substep kcount runs next, in stream order after this
+  __shared__ int s_box[4];
+  __shared__ int s_bad;
+  __shared__ double s_pose[8];
 #ifdef SBT_PERSISTENT_TU
-  const int64_t k = ld_fresh(cp.kcount) + j;  // written earlier in the same launch
+  const int64_t k0 = ld_fresh(cp.kcount);  // written earlier in the same launch
 #else
-  const int64_t k = *cp.kcount + j;
+  // the forcing loop beside this one may have counted up already
+  int64_t k0 = ld_fresh(cp.kcount);
+  if (a.beside >= 0 && (int)(k0 & cp.plan_mask) != a.beside) --k0;
 #endif
+  const int64_t k = k0 + a.first + j;
   const int b = (int)(k & cp.plan_mask);
   const PlanView P = plan_view(cp, b);
+  auto put_header = [&](int cells, int status) {
+    if (tid == 0) *reinterpret_cast<int4 *>(P.hdr) = make_int4((int)k, cells, status, cp.body_kind == 0);
+  };
 
   // 1. kinematics: r_j(t_k), desired velocity (r_j(t_k+1) - r_j(t_k)) / dt,
   //    and the Peskin weights of the marker's 4x4 stencil
+  constexpr int LPM = PAIR ? 2 : 1, NA = 3 - LPM;  // lanes per marker, axes per lane
+  const int m = tid / LPM, ax = tid % LPM;
+  const bool own = m < n;
+  const bool own_wave = wave * 64 < n * LPM;
+  double xb = 0.0, yb = 0.0, hu[NA] = {};
+  const int kind = cp.body_kind;
+  if (own) {
+    xb = cp.xb[m];
+    yb = cp.yb[m];
+    if (kind == 2) {
+#pragma unroll
+      for (int q = 0; q < NA; ++q) hu[q] = cp.hud[(ax + q) * nm + m];
+    }
+  }
   if (tid == 0) {
     s_box[0] = 1 << 30; s_box[1] = 1 << 30; s_box[2] = -(1 << 30); s_box[3] = -(1 << 30);
-    s_ns = 0;
     s_bad = 0;
-    s_pose[0] = body_pose(cp, (double)k);
-  } else if (tid == 64) {
-    s_pose[1] = body_pose(cp, (double)(k + 1));
+    s_over = 0;
   }
+  if (tid < kBins) s_bin[tid] = 0;
+  if (lane == 0 && wave < 8 && kind != 2) s_pose[wave] = body_pose(cp, (double)(k + (wave >> 2)), wave & 3);
   __syncthreads();
-  const bool own = tid < n;
-  int i0 = 0, j0 = 0;
-  int bx0 = 1 << 30, by0 = 1 << 30, bx1 = -(1 << 30), by1 = -(1 << 30);
-  if (own) {
-    double X, Y;
-    if (cp.body_kind == 2) {  // caller-placed markers with given desired velocity
-      X = cp.xb[tid];
-      Y = cp.yb[tid];
-      P.ud[tid] = cp.hud[tid];
-      P.ud[nm + tid] = cp.hud[nm + tid];
-    } else {
-      double X1, Y1;
-      marker_position(cp, s_pose[0], tid, X, Y);
-      marker_position(cp, s_pose[1], tid, X1, Y1);
-      P.ud[tid] = X1 - X;
-      P.ud[nm + tid] = Y1 - Y;
-    }
-    i0 = tap0(X);
-    j0 = tap0(Y);
-    P.i0[tid] = i0;
-    P.j0[tid] = j0;
+  int t0[2] = {0, 0};  // first tap, x and y
+  if (own_wave) {
+    int lo[NA], hi[NA];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      P.w[(size_t)t * nm + tid] = peskin(i0 + t + 0.5 - X);
-      P.w[(size_t)(4 + t) * nm + tid] = peskin(j0 + t + 0.5 - Y);
-    }
-    bx0 = i0; by0 = j0; bx1 = i0 + 4; by1 = j0 + 4;
-  }
+    for (int q = 0; q < NA; ++q) {
+      const int axis = ax + q;
+      lo[q] = 1 << 30;
+      hi[q] = -(1 << 30);
+      if (own) {
+        double X, ud;
+        if (kind == 2) {  // caller-placed markers with given desired velocity
+          X = axis == 0 ? xb : yb;
+          ud = hu[q];
+        } else {
+          const Pose p0 = {s_pose[0], s_pose[1], s_pose[2], s_pose[3]}, p1 = {s_pose[4], s_pose[5], s_pose[6], s_pose[7]};
+          X = marker_position(kind, p0, xb, yb, axis);
+          ud = marker_position(kind, p1, xb, yb, axis) - X;
+        }
+        P.ud[axis * nm + m] = ud;
+        const int i0 = tap0(X);
+        double2 *w = reinterpret_cast<double2 *>(P.w + (size_t)m * 8 + 4 * axis);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    bx0 = min(bx0, __shfl_xor(bx0, o, 64));
-    by0 = min(by0, __shfl_xor(by0, o, 64));
-    bx1 = max(bx1, __shfl_xor(bx1, o, 64));
-    by1 = max(by1, __shfl_xor(by1, o, 64));
+        for (int t = 0; t < 4; t += 2) w[t / 2] = make_double2(peskin(i0 + t + 0.5 - X), peskin(i0 + t + 1 + 0.5 - X));
+        lo[q] = i0;
+        hi[q] = i0 + 4;
+        t0[q] = i0;
+      }
+    }
+    if (PAIR) {  // both lanes of a marker get both first taps
+      const int other = __shfl_xor(t0[0], 1, 64);
+      t0[1] = ax == 0 ? other : t0[0];
+      t0[0] = ax == 0 ? t0[0] : other;
+    }
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+#pragma unroll
+      for (int o = 32; o >= LPM; o >>= 1) {
+        lo[q] = min(lo[q], __shfl_xor(lo[q], o, 64));
+        hi[q] = max(hi[q], __shfl_xor(hi[q], o, 64));
+      }
+      if (lane < LPM) {
+        atomicMin(&s_box[ax + q], lo[q]);
+        atomicMax(&s_box[2 + ax + q], hi[q]);
+      }
+    }
   }
-  if (lane == 0) {
-    atomicMin(&s_box[0], bx0);
-    atomicMin(&s_box[1], by0);
-    atomicMax(&s_box[2], bx1);
-    atomicMax(&s_box[3], by1);
-  }
+  const int i0 = t0[0], j0 = t0[1];
+  if (own && ax == 0) P.ij[m] = (i0 & 0xffff) | (j0 << 16);
   __syncthreads();
   const int wx0 = s_box[0], wy0 = s_box[1];
   const int ww = s_box[2] - wx0, wh = s_box[3] - wy0;
@@ -1652,8 +1743,8 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
     if (tid == 0) {
       IbmWindow e = {0, 0, 0, 0};
       cp.win[b] = e;
-      P.hdr[0] = (int)k; P.hdr[1] = 0; P.hdr[2] = ERR_WINDOW;
     }
+    put_header(0, ERR_WINDOW);
     return;
   }
   if (tid == 0) {
@@ -1668,116 +1759,149 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
   auto count_of = [&](int c) -> int { return (int)((cnt[c >> 1] >> ((c & 1) << 4)) & 0xffffu); };
   {
     double *F = cp.wF + (size_t)b * 2 * cp.win_cap;
+    for (int w = tid; w < (ncell + 1) / 2; w += MDF_THREADS) cnt[w] = 0u;
     for (int c = tid; c < ncell; c += MDF_THREADS) {
       F[c] = 0.0;
       F[(size_t)cp.win_cap + c] = 0.0;
     }
-    for (int w = tid; w < (ncell + 1) / 2; w += MDF_THREADS) cnt[w] = 0u;
   }
   __syncthreads();
-  // 3. every marker lane registers its 16 taps: its slot in each cell's
-  //    contributor list, and the first toucher of a cell appends the cell
-  //    to the compact list (a wavefront prefix sum sizes the append).
-  //    cidx(t): window index of tap t; pos(t): its slot in that cell's
-  //    contributor list (16 bits, two per word)
-  auto cidx = [&](int t) { return (j0 + (t >> 2) - wy0) * ww + (i0 + (t & 3) - wx0); };
-  uint32_t pos2[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  auto pos = [&](int t) { return (int)((pos2[t >> 1] >> ((t & 1) << 4)) & 0xffffu); };
-  {
-    int nf = 0;
-    if (own) {
+  // 3. every marker registers its 16 taps (two rows per lane with PAIR): its
+  //    slot in each cell's contributor list
+  //    cidx(t): window index of the lane's tap t; pos(t): its slot in that
+  //    cell's contributor list (16 bits, two per word)
+  constexpr int NT = 16 / LPM;
+  const int tap_a = ax * NT;
+  auto cidx = [&](int t) { return (j0 + ((tap_a + t) >> 2) - wy0) * ww + (i0 + (t & 3) - wx0); };
+  uint32_t pos2[NT / 2] = {};
+  auto half = [](const uint32_t *w, int t) { return (int)((w[t >> 1] >> ((t & 1) << 4)) & 0xffffu); };
+  if (own) {
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
-        const int c = cidx(t), sh = (c & 1) << 4;  // counts stay below 2^16 (at most one per marker)
-        const uint32_t p = (atomicAdd(&cnt[c >> 1], 1u << sh) >> sh) & 0xffffu;
-        if (t & 1) pos2[t >> 1] |= p << 16;
-        else pos2[t >> 1] = p;
-      }
-#pragma unroll
-      for (int t = 0; t < 16; ++t) nf += pos(t) == 0;
+    for (int t = 0; t < NT; ++t) {
+      const int c = cidx(t), sh = (c & 1) << 4;  // counts stay below 2^16 (at most one per marker)
+      pos2[t >> 1] |= ((atomicAdd(&cnt[c >> 1], 1u << sh) >> sh) & 0xffffu) << ((t & 1) << 4);
     }
-    int incl = nf;
+  }
+  __syncthreads();
+  // 4. every stencil cell gets its number among the cells of its count, then
+  //    its place q in descending order of counts and, in window order, its
+  //    place g in the order the forcing loop gathers in (neighbouring lanes
+  //    read neighbouring cells).  A window in LDS is scanned, a chunk of 64
+  //    cells at a time, each wave a run of chunks; beyond LDS the first
+  //    toucher of a cell speaks for it, and g follows the markers.
+  const int chunks = (ncell + 63) / 64, ch0 = chunks * wave / 16, ch1 = chunks * (wave + 1) / 16;
+  auto scan = [&](auto &&visit) {
+    if (in_lds) {
+      for (int ch = ch0; ch < ch1; ++ch) {
+        const int c = ch * 64 + lane;
+        const int n_c = c < ncell ? count_of(c) : 0;
+        visit(c, n_c, __ballot(n_c > 0));
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int c = cidx(t);
+        const int n_c = own && half(pos2, t) == 0 ? count_of(c) : 0;
+        visit(c, n_c, __ballot(n_c > 0));
+      }
+    }
+  };
+  {
+    int mine = 0;
+    scan([&](int c, int n_c, unsigned long long touched) {
+      mine += __popcll(touched);
+      if (n_c > 0) idx[c] = (uint16_t)atomicAdd(&s_bin[min(n_c, kBins - 1)], 1);
+    });
+    if (lane == 0) s_wsum[wave] = mine;
+  }
+  __syncthreads();
+  if (wave == 0) {  // descending counts: bin kBins - 1 - lane
+    const int bin = kBins - 1 - lane, c = s_bin[bin];
+    int q = c, l = bin == kBins - 1 ? 0 : c * bin;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      int v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
+      const int uq = __shfl_up(q, o, 64), ul = __shfl_up(l, o, 64);
+      if (lane >= o) {
+        q += uq;
+        l += ul;
+      }
     }
-    const int total = __shfl(incl, 63, 64);
-    int base = 0;
-    if (lane == 63 && total > 0) base = atomicAdd(&s_ns, total);
-    base = __shfl(base, 63, 64);
-    if (own) {
-      int q = base + incl - nf;
-#pragma unroll
-      for (int t = 0; t < 16; ++t)
-        if (pos(t) == 0) {
-          if (q < cap) s_cells[q] = cidx(t);
-          idx[cidx(t)] = (uint16_t)q;
-          ++q;
-        }
-    }
+    const int others = __shfl(l, 63, 64);  // lists of the last bin follow all others
+    s_binq[bin] = q - c;
+    s_binc[bin] = bin == kBins - 1 ? others : l - c * bin;
+    if (lane == 63) s_bin[0] = q;  // stencil cells in all
   }
   __syncthreads();
-  const int ns = s_ns;
+  const int ns = s_bin[0];
   if (ns > cap) {
-    if (tid == 0) {
-      P.hdr[0] = (int)k; P.hdr[1] = 0; P.hdr[2] = ERR_CONTRIB;
-    }
+    put_header(0, ERR_CONTRIB);
     return;
   }
-  // 4. CSR starts: exclusive prefix sum of the contributor counts over the
-  //    compact cells (each lane sums a contiguous run, then a block scan)
+  uint16_t *s_gq = s_list;  // [ns] place q of the cell in place g, until the lists are filled (ns <= 16 n)
   {
-    const int per = (ns + MDF_THREADS - 1) / MDF_THREADS;
-    const int q0 = min(ns, tid * per), q1 = min(ns, q0 + per);
-    int sum = 0;
-    for (int q = q0; q < q1; ++q) sum += count_of(s_cells[q]);
-    int incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      int v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
-    }
-    if (lane == 63) s_wsum[wave] = incl;
-    __syncthreads();
-    int wbase = 0;
-    for (int w = 0; w < wave; ++w) wbase += s_wsum[w];
-    int run = wbase + incl - sum;
-    for (int q = q0; q < q1; ++q) {
-      s_start[q] = run;
-      run += count_of(s_cells[q]);
-    }
+    int g = 0;
+    for (int w = 0; w < wave; ++w) g += s_wsum[w];
+    scan([&](int c, int n_c, unsigned long long touched) {
+      if (n_c > 0) {
+        const int bin = min(n_c, kBins - 1), r = idx[c];
+        const int q = s_binq[bin] + r;
+        s_cells[q] = c;
+        s_start[q] = s_binc[bin] + (bin < kBins - 1 ? r * n_c : atomicAdd(&s_over, n_c));
+        idx[c] = (uint16_t)q;
+        s_gq[g + __popcll(touched & ((1ull << lane) - 1ull))] = (uint16_t)q;
+      }
+      g += __popcll(touched);
+    });
+  }
+  __syncthreads();
+  // the gather records: the blocks holding the cell and its streaming
+  // sources (the 3x3 neighbourhood spans at most 2x2 blocks, found at its
+  // corners; all must be owned finest blocks)
+  for (int g = tid; g < ns; g += MDF_THREADS) {
+    const int q = s_gq[g], c = s_cells[q];
+    const int cy = c / ww, gx = wx0 + c - cy * ww, gy = wy0 + cy;
+    const int sw = finest_block(cp, gx - 1, gy - 1), se = finest_block(cp, gx + 1, gy - 1);
+    const int nw = finest_block(cp, gx - 1, gy + 1), ne = finest_block(cp, gx + 1, gy + 1);
+    if (sw < 0 || se < 0 || nw < 0 || ne < 0) s_bad = 1;
+    int32_t *R = P.cell + (size_t)g * 8;
+    *reinterpret_cast<int4 *>(R) = make_int4(sw, se, nw, ne);
+    *reinterpret_cast<int2 *>(R + 4) = make_int2(gx | (gy << 16), q);
   }
   __syncthreads();
   // 5. fill the contributor lists (slot order is arbitrary) and the
   //    marker-side map from each tap to its stencil cell
   if (own) {
+    uint32_t tap[NT / 2] = {};
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
+    for (int t = 0; t < NT; ++t) {
       const int q = idx[cidx(t)];
-      s_list[s_start[q] + pos(t)] = (uint16_t)tid;
-      P.tap[(size_t)t * nm + tid] = (uint16_t)q;
+      s_list[s_start[q] + half(pos2, t)] = (uint16_t)m;
+      tap[t >> 1] |= (uint32_t)q << ((t & 1) << 4);
     }
+    uint4 *T = reinterpret_cast<uint4 *>(P.tap + (size_t)m * 16 + tap_a);
+#pragma unroll
+    for (int t = 0; t < NT / 8; ++t) T[t] = make_uint4(tap[4 * t], tap[4 * t + 1], tap[4 * t + 2], tap[4 * t + 3]);
   }
   __syncthreads();
   // 6. per stencil cell: contributors in ascending marker index (the
-  //    spreading sums in marker order), the blocks holding the cell and its
-  //    streaming sources (the 3x3 neighbourhood spans at most 2x2 blocks,
-  //    found at its corners; all must be owned finest blocks)
+  //    spreading sums in marker order)
   for (int q = tid; q < ns; q += MDF_THREADS) {
     const int c = s_cells[q];
     const int n_c = count_of(c), st = s_start[q];
-    const int gx = wx0 + c % ww, gy = wy0 + c / ww;
+    const int cy = c / ww, gx = wx0 + c - cy * ww, gy = wy0 + cy;
+    *reinterpret_cast<int2 *>(P.cell + (size_t)q * 8 + 6) = make_int2(st | (n_c << 16), gx | (gy << 16));
     uint16_t *L = s_list + st;
     uint16_t *O = P.list + st;
-    if (n_c <= 16) {
-      int v[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) v[r] = r < n_c ? (int)L[r] : 0x7fffffff;
-      sort_net<16>(v);
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (r < n_c) O[r] = (uint16_t)v[r];
+    // the wave's first cell has its largest count
+    const int most = __builtin_amdgcn_readfirstlane(n_c);
+    if (most <= 1) {
+      O[0] = L[0];
+    } else if (most <= 4) {
+      sort_out<4>(L, O, n_c);
+    } else if (most <= 8) {
+      sort_out<8>(L, O, n_c);
+    } else if (most <= 16) {
+      sort_out<16>(L, O, n_c);
     } else {  // rare: more than 16 markers over one cell (insertion sort in LDS)
       for (int r = 1; r < n_c; ++r) {
         uint16_t v = L[r];
@@ -1790,25 +1914,14 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
       }
       for (int r = 0; r < n_c; ++r) O[r] = L[r];
     }
-    const int sw = finest_block(cp, gx - 1, gy - 1), se = finest_block(cp, gx + 1, gy - 1);
-    const int nw = finest_block(cp, gx - 1, gy + 1), ne = finest_block(cp, gx + 1, gy + 1);
-    if (sw < 0 || se < 0 || nw < 0 || ne < 0) s_bad = 1;
-    int4 r0 = {c, sw, se, nw};
-    int4 r1 = {ne, st, n_c, 0};
-    int4 *R = reinterpret_cast<int4 *>(P.cell + (size_t)q * 8);
-    R[0] = r0;
-    R[1] = r1;
   }
   __syncthreads();
-  if (tid == 0) {
-    P.hdr[0] = (int)k;
-    P.hdr[1] = ns;
-    P.hdr[2] = s_bad ? ERR_MARKER : 0;
-  }
+  put_header(ns, s_bad ? ERR_MARKER : 0);
 }
 
 #ifndef SBT_PERSISTENT_TU
-__global__ __launch_bounds__(MDF_THREADS, 8) void ibm_prep_kernel(IbmArgs a) { prep_item(a, blockIdx.x); }
+template <bool PAIR>
+__global__ __launch_bounds__(MDF_THREADS, 8) void ibm_prep_kernel(IbmArgs a) { prep_item<PAIR, PAIR>(a, blockIdx.x); }
 #endif
 
 __device__ __forceinline__ void mdf_fail(const CaseDev &cp, int *err, int code, int64_t k) {
@@ -1819,10 +1932,7 @@ __device__ __forceinline__ void mdf_fail(const CaseDev &cp, int *err, int code, 
 }
 
 constexpr int kCellsPerLane = 4;  // stencil cells owned per lane (cell_cap <= 4096)
-#ifndef SBT_MDF_CACHED
-#define SBT_MDF_CACHED 12
-#endif
-constexpr int kCached = SBT_MDF_CACHED;  // contributors whose weights a lane keeps in registers
+constexpr int kCached = 12;  // contributors whose weights a lane keeps in registers
 
 // Block of the finest cell (sx, sy) inside the 3x3 neighbourhood of (gx, gy),
 // from the four corner blocks of that neighbourhood.
@@ -1831,9 +1941,39 @@ __device__ __forceinline__ int corner_block(int gx, int gy, int sx, int sy, int 
   return west ? (south ? sw : nw) : (south ? se : ne);
 }
 
+// Contributors [e0, e0 + 4) of a stencil cell at (gx, gy) whose list starts
+// at st: the markers' indices and the weights w_x w_y.  Every load of a kind
+// is issued before the next kind needs it.  Past the last contributor (cnt)
+// it is repeated with weight 0: adding a product of 0 leaves the sum as it
+// is, and a force that is not finite has reached the cell already.
+__device__ __forceinline__ void cell_weights(const uint16_t *s_list, const int *s_ij, const double *s_wx, const double *s_wy,
+                                             int NM, int st, int cnt, int e0, int gx, int gy, int (&j)[4],
+                                             double (&w)[4]) {
+#pragma clang fp contract(off)
+  int ij[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) j[e] = s_list[st + max(min(e0 + e, cnt - 1), 0)];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) ij[e] = s_ij[j[e]];
+  double wx[4], wy[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int dx = (gx - (short)(ij[e] & 0xffff)) & 3, dy = (gy - (ij[e] >> 16)) & 3;
+    wx[e] = s_wx[dx * NM + j[e]];
+    wy[e] = s_wy[dy * NM + j[e]];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) w[e] = e0 + e < cnt ? wx[e] * wy[e] : 0.0;
+}
+
 // The forcing loop of body `body` (one 1024-lane workgroup); arguments by
-// value for the same reason as prep_item's.
-template <int ST>
+// value for the same reason as prep_item's.  With PAIR two lanes share a
+// marker, one per velocity component (bodies of up to 512 markers).
+// Latency bounds it: a chain of two plan loads, one gather, and 2 N_F phases
+// over LDS with a barrier each.  A phase's loads are issued together, ahead
+// of the sums that use them in order, and what does not change in the loop
+// stays in registers.
+template <int ST, bool PAIR>
 __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
 #pragma clang fp contract(off)
   const CaseDev &cp = a.bodies[body];
@@ -1844,15 +1984,14 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
   extern __shared__ __align__(16) double lds[];
   double2 *s_dF = reinterpret_cast<double2 *>(lds);  // [NM] marker force of the iteration
   double2 *s_uv = s_dF + NM;        // [CC] corrected velocity of the cell
-  double *s_wx = reinterpret_cast<double *>(s_uv + CC);  // [4][NM]
+  double *s_rho = reinterpret_cast<double *>(s_uv + CC);  // [CC]
+  double *s_wx = s_rho + CC;        // [4][NM]
   double *s_wy = s_wx + 4 * NM;     // [4][NM]
-  double *s_ds = s_wy + 4 * NM;     // [NM]
-  double *s_rho = s_ds + NM;        // [CC]
-  double *s_fx = s_rho + CC;        // [CC] accumulated force of the cell
+  uint16_t *s_list = reinterpret_cast<uint16_t *>(s_wy + 4 * NM);  // [16 NM], 16-byte aligned (CC is a multiple of 4)
+  double *s_ds = reinterpret_cast<double *>(s_list + 16 * NM);  // [NM]
+  double *s_fx = s_ds + NM;         // [CC] accumulated force of the cell
   double *s_fy = s_fx + CC;         // [CC]
-  int *s_i0 = reinterpret_cast<int *>(s_fy + CC);  // [NM]
-  int *s_j0 = s_i0 + NM;
-  uint16_t *s_list = reinterpret_cast<uint16_t *>(s_j0 + NM);  // [16 NM]
+  int *s_ij = reinterpret_cast<int *>(s_fy + CC);  // [NM] first tap, x | y << 16
   // The plan buffer is the substep's parity (known to the launcher), so the
   // plan loads below do not wait for the substep counter.
   const int b = a.parity;
@@ -1873,10 +2012,10 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
   //    global->LDS copies, 16 bytes per lane) and the marker tables
   const int cap = min(cp.cell_cap, min(CC, kCellsPerLane * MDF_THREADS));
   int4 rec0[kCellsPerLane], rec1[kCellsPerLane];
+  const int4 *R = reinterpret_cast<const int4 *>(P.cell);
   if (tid < cap) {
-    const int4 *R = reinterpret_cast<const int4 *>(P.cell + (size_t)tid * 8);
-    rec0[0] = R[0];
-    rec1[0] = R[1];
+    rec0[0] = R[2 * tid];
+    rec1[0] = R[2 * tid + 1];
   }
   {
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1889,69 +2028,88 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
                                          (lds_void *)(reinterpret_cast<char *>(s_list) + (size_t)v0 * 16), 16, 0, 0);
     }
   }
-  const bool own = tid < n;
+  // lane's marker m and the components it works on: comp (PAIR) or both
+  constexpr int NC = PAIR ? 1 : 2;
+  const int m = PAIR ? tid >> 1 : tid, comp = PAIR ? tid & 1 : 0;
+  const bool own = m < n;
   double wxr[4] = {0.0, 0.0, 0.0, 0.0}, wyr[4] = {0.0, 0.0, 0.0, 0.0};
-  double udx = 0.0, udy = 0.0, dsr = 0.0;
-  int i0r = 0, j0r = 0;
+  double ud[NC] = {}, dsr = 0.0;
+  int ij = 0;
   uint32_t taps[8];  // stencil cells of the 16 taps, two per word
   if (own) {
+    // 16-byte loads of the marker's own record: instruction issue, with 4
+    // waves per SIMD, costs this phase more than the bytes do
+    const double2 *w = reinterpret_cast<const double2 *>(P.w + (size_t)m * 8);
+    const uint4 *T = reinterpret_cast<const uint4 *>(P.tap + (size_t)m * 16);
+    const double2 w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
+    const uint4 ta = T[0], tb = T[1];
+    wxr[0] = w0.x; wxr[1] = w0.y; wxr[2] = w1.x; wxr[3] = w1.y;
+    wyr[0] = w2.x; wyr[1] = w2.y; wyr[2] = w3.x; wyr[3] = w3.y;
+    taps[0] = ta.x; taps[1] = ta.y; taps[2] = ta.z; taps[3] = ta.w;
+    taps[4] = tb.x; taps[5] = tb.y; taps[6] = tb.z; taps[7] = tb.w;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      wxr[t] = P.w[(size_t)t * nm + tid];
-      wyr[t] = P.w[(size_t)(4 + t) * nm + tid];
-    }
-    udx = P.ud[tid];
-    udy = P.ud[nm + tid];
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-      taps[t] = (uint32_t)P.tap[(size_t)(2 * t) * nm + tid] | ((uint32_t)P.tap[(size_t)(2 * t + 1) * nm + tid] << 16);
-    i0r = P.i0[tid];
-    j0r = P.j0[tid];
-    dsr = cp.ds[tid];
+    for (int c = 0; c < NC; ++c) ud[c] = P.ud[(size_t)(comp + c) * nm + m];
+    ij = P.ij[m];
+    dsr = cp.ds[m];
   }
   const int ns = hdr.y;
   int status = hdr.z;
-  if (hdr.x != (int)k || (k & cp.plan_mask) != b) status = ERR_PLAN;
+  // a fixed body's plan serves every substep
+  if (!hdr.w && (hdr.x != (int)k || (k & cp.plan_mask) != b)) status = ERR_PLAN;
   if (!status && ns > cap) status = ERR_CONTRIB;
   if (status) {
     if (tid == 0) mdf_fail(cp, a.err, status, k);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // the list copies land before the LDS is released
     return;
   }
+#pragma unroll
+  for (int r = 1; r < kCellsPerLane; ++r) {
+    const int q = tid + r * MDF_THREADS;
+    if (q < ns) {
+      rec0[r] = R[2 * q];
+      rec1[r] = R[2 * q + 1];
+    }
+  }
   // 2. moments of the owned stencil cells from the post-stream populations
   //    (the initial state is read in place): rho and the uncorrected
-  //    velocity to LDS
+  //    velocity to LDS; the gathers of two cells per lane are in flight
   const int l = cp.n_levels - 1;
+  //    (the lane gathers the cell in place tid of the gather order and
+  //    spreads to the one in place tid of the order by count)
   int cxy[kCellsPerLane], csc[kCellsPerLane];  // gx | gy << 16, list start | count << 16
 #pragma unroll
-  for (int r = 0; r < kCellsPerLane; ++r) {
-    const int q = tid + r * MDF_THREADS;
-    cxy[r] = 0;
-    csc[r] = 0;
-    if (q < ns) {
-      if (r > 0) {
-        const int4 *R = reinterpret_cast<const int4 *>(P.cell + (size_t)q * 8);
-        rec0[r] = R[0];
-        rec1[r] = R[1];
-      }
-      const int4 r0 = rec0[r], r1 = rec1[r];
-      const int c = r0.x;
-      const int gx = win.x0 + c % win.w, gy = win.y0 + c / win.w;
-      cxy[r] = gx | (gy << 16);
-      csc[r] = r1.y | (r1.z << 16);
-      double f[9];
-      if (a.first) {
-        const int ob = corner_block(gx, gy, gx, gy, r0.y, r0.z, r0.w, r1.x);
+  for (int r0 = 0; r0 < kCellsPerLane; r0 += 2) {
+    typename Store<ST>::T g[2][9];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) f[i] = (double)ldv<ST>(a.src, ob, i, (gy & 15) * 16 + (gx & 15));
+    for (int h = 0; h < 2; ++h) {
+      const int r = r0 + h;
+      cxy[r] = 0;
+      csc[r] = 0;
+      if (tid + r * MDF_THREADS >= ns) continue;
+      const int4 c0 = rec0[r], c1 = rec1[r];
+      const int gx = c1.x & 0xffff, gy = c1.x >> 16;
+      csc[r] = c1.z;
+      cxy[r] = c1.w;
+      if (a.first) {
+        const int ob = corner_block(gx, gy, gx, gy, c0.x, c0.y, c0.z, c0.w);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) g[h][i] = ldraw<ST>(a.src, ob, i, (gy & 15) * 16 + (gx & 15));
       } else {
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
           const int sx = gx - CX[i], sy = gy - CY[i];
-          const int nb = corner_block(gx, gy, sx, sy, r0.y, r0.z, r0.w, r1.x);
-          f[i] = (double)ldv<ST>(a.src, nb, i, (sy & 15) * 16 + (sx & 15));
+          const int nb = corner_block(gx, gy, sx, sy, c0.x, c0.y, c0.z, c0.w);
+          g[h][i] = ldraw<ST>(a.src, nb, i, (sy & 15) * 16 + (sx & 15));
         }
       }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (tid + (r0 + h) * MDF_THREADS >= ns) continue;
+      const int q = rec1[r0 + h].y;
+      double f[9];
+#pragma unroll
+      for (int i = 0; i < 9; ++i) f[i] = (double)Store<ST>::ld(g[h][i]);
       double rho, jx, jy;
       moments64(f, rho, jx, jy);
       if constexpr (Store<ST>::kShift) rho = cp.rho0 + rho;
@@ -1965,12 +2123,11 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
   if (own) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      s_wx[t * NM + tid] = wxr[t];
-      s_wy[t * NM + tid] = wyr[t];
+      if (!PAIR || comp == 0) s_wx[t * NM + m] = wxr[t];
+      if (!PAIR || comp == 1) s_wy[t * NM + m] = wyr[t];
     }
-    s_i0[tid] = i0r;
-    s_j0[tid] = j0r;
-    s_ds[tid] = dsr;
+    s_ij[m] = ij;
+    s_ds[m] = dsr;
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the list copies
   __syncthreads();
@@ -1980,60 +2137,71 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
   // indices: held in registers for the lane's first cell, so such a
   // contribution of an iteration reads only the marker's force and arc
   // length (LDS); further contributors are looked up in LDS.
+  auto tap_weight = [&](int t) -> double {
+    return PAIR ? wxr[t & 3] * wyr[t >> 2] : s_wx[(t & 3) * NM + m] * s_wy[(t >> 2) * NM + m];
+  };
+  auto tap_cell = [&](int t) -> int { return (taps[t >> 1] >> ((t & 1) * 16)) & 0xffff; };
   double sr = 0.0;
   if (own) {
 #pragma unroll
-    for (int bb = 0; bb < 4; ++bb) {
-      const double py = s_wy[bb * NM + tid];
+    for (int t0 = 0; t0 < 16; t0 += 8) {
+      double v[8];
 #pragma unroll
-      for (int aa = 0; aa < 4; ++aa) {
-        const int t = bb * 4 + aa;
-        const int q = (taps[t >> 1] >> ((t & 1) * 16)) & 0xffff;
-        sr += s_rho[q] * (s_wx[aa * NM + tid] * py);
-      }
+      for (int t = 0; t < 8; ++t) v[t] = s_rho[tap_cell(t0 + t)];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) sr += v[t] * tap_weight(t0 + t);
     }
   }
-  auto weight = [&](int j, int gx, int gy) -> double {
-    return s_wx[(gx - s_i0[j]) * NM + j] * s_wy[(gy - s_j0[j]) * NM + j];
-  };
   const int cnt0 = tid < ns ? csc[0] >> 16 : 0;
   double cw[kCached];
   uint32_t cj[kCached / 2];
 #pragma unroll
-  for (int e = 0; e < kCached / 2; ++e) cj[e] = 0;
+  for (int e0 = 0; e0 < kCached; e0 += 4) {
+    cj[e0 / 2] = cj[e0 / 2 + 1] = 0;
 #pragma unroll
-  for (int e = 0; e < kCached; ++e) {
-    cw[e] = 0.0;
-    if (e < cnt0) {
-      const int j = s_list[(csc[0] & 0xffff) + e];
-      cw[e] = weight(j, cxy[0] & 0xffff, cxy[0] >> 16);
-      cj[e >> 1] |= (uint32_t)j << ((e & 1) * 16);
+    for (int e = 0; e < 4; ++e) cw[e0 + e] = 0.0;
+    if (__any(cnt0 > e0)) {
+      int j[4];
+      double w[4];
+      cell_weights(s_list, s_ij, s_wx, s_wy, NM, csc[0] & 0xffff, cnt0, e0, cxy[0] & 0xffff, cxy[0] >> 16, j, w);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cw[e0 + e] = w[e];
+      cj[e0 / 2] = (uint32_t)j[0] | ((uint32_t)j[1] << 16);
+      cj[e0 / 2 + 1] = (uint32_t)j[2] | ((uint32_t)j[3] << 16);
     }
   }
   // 3. N_F iterations: interpolate (Eq. 12), boundary force (Eq. 11),
   //    spread (Eq. 15), correct velocity and accumulate force
-  double ftx = 0.0, fty = 0.0;
-  for (int it = 0; it < cp.mdf_iters; ++it) {
+  double ft[NC] = {};
+  const int iters = cp.mdf_iters;
+  for (int it = 0; it < iters; ++it) {
+    const bool last = it + 1 == iters;
+    // opaque in every iteration: the products and addresses formed from
+    // these, hoisted out of the loop, would not fit the registers
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (PAIR) asm volatile("" : "+v"(wxr[t]), "+v"(wyr[t]));
+      asm volatile("" : "+v"(taps[t]), "+v"(taps[4 + t]));
+    }
+#pragma unroll
+    for (int e = 0; e < kCached / 2; ++e) asm volatile("" : "+v"(cj[e]));
     if (own) {
-      double su = 0.0, sv = 0.0;
 #pragma unroll
-      for (int bb = 0; bb < 4; ++bb) {
-        const double py = s_wy[bb * NM + tid];
+      for (int c = 0; c < NC; ++c) {
+        const double *u = reinterpret_cast<const double *>(s_uv) + comp + c;
+        double s = 0.0;
 #pragma unroll
-        for (int aa = 0; aa < 4; ++aa) {
-          const int t = bb * 4 + aa;
-          const int q = (taps[t >> 1] >> ((t & 1) * 16)) & 0xffff;
-          const double w = s_wx[aa * NM + tid] * py;
-          const double2 uv = s_uv[q];
-          su += uv.x * w;
-          sv += uv.y * w;
+        for (int t0 = 0; t0 < 16; t0 += 8) {
+          double v[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) v[t] = u[2 * tap_cell(t0 + t)];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) s += v[t] * tap_weight(t0 + t);
         }
+        const double g = 2.0 * sr * (ud[c] - s);
+        reinterpret_cast<double *>(s_dF)[2 * m + comp + c] = g;
+        ft[c] += g;
       }
-      const double gx = 2.0 * sr * (udx - su);
-      const double gy = 2.0 * sr * (udy - sv);
-      s_dF[tid] = make_double2(gx, gy);
-      ftx += gx;
-      fty += gy;
     }
     __syncthreads();
 #pragma unroll
@@ -2041,69 +2209,54 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
       const int q = tid + r * MDF_THREADS;
       if (q < ns) {
         double dfx = 0.0, dfy = 0.0;
+        auto add4 = [&](const int (&j)[4], const double (&w)[4]) {
+          double2 d[4];
+          double ds[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            d[e] = s_dF[j[e]];
+            ds[e] = s_ds[j[e]];
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            dfx += d[e].x * w[e] * ds[e];
+            dfy += d[e].y * w[e] * ds[e];
+          }
+        };
+        const int gx = cxy[r] & 0xffff, gy = cxy[r] >> 16, st = csc[r] & 0xffff;
+        const int cnt = r == 0 ? cnt0 : csc[r] >> 16;
         if (r == 0) {
 #pragma unroll
-          for (int e = 0; e < kCached; ++e)
-            if (e < cnt0) {
-              const int j = (cj[e >> 1] >> ((e & 1) * 16)) & 0xffff;
-              const double2 d = s_dF[j];
-              const double dsj = s_ds[j];
-              dfx += d.x * cw[e] * dsj;
-              dfy += d.y * cw[e] * dsj;
+          for (int e0 = 0; e0 < kCached; e0 += 4)
+            if (__any(cnt > e0)) {
+              const int j[4] = {(int)(cj[e0 / 2] & 0xffff), (int)(cj[e0 / 2] >> 16), (int)(cj[e0 / 2 + 1] & 0xffff),
+                                (int)(cj[e0 / 2 + 1] >> 16)};
+              const double w[4] = {cw[e0], cw[e0 + 1], cw[e0 + 2], cw[e0 + 3]};
+              add4(j, w);
             }
-          // contributors beyond the cached ones, in the same ascending order
-          const int gx = cxy[0] & 0xffff, gy = cxy[0] >> 16, st = csc[0] & 0xffff;
-          for (int e = kCached; e < cnt0; ++e) {
-            const int j = s_list[st + e];
-            const double2 d = s_dF[j];
-            const double w = weight(j, gx, gy), dsj = s_ds[j];
-            dfx += d.x * w * dsj;
-            dfy += d.y * w * dsj;
-          }
-        } else {  // a lane's further cells
-          const int gx = cxy[r] & 0xffff, gy = cxy[r] >> 16;
-          const int st = csc[r] & 0xffff, cnt = csc[r] >> 16;
-          for (int e = 0; e < cnt; ++e) {
-            const int j = s_list[st + e];
-            const double2 d = s_dF[j];
-            const double w = weight(j, gx, gy), dsj = s_ds[j];
-            dfx += d.x * w * dsj;
-            dfy += d.y * w * dsj;
-          }
+        }
+        // contributors beyond the cached ones and those of a lane's further
+        // cells, in the same ascending order
+        for (int e0 = r == 0 ? kCached : 0; e0 < cnt; e0 += 4) {
+          int j[4];
+          double w[4];
+          cell_weights(s_list, s_ij, s_wx, s_wy, NM, st, cnt, e0, gx, gy, j, w);
+          add4(j, w);
         }
         s_fx[q] = s_fx[q] + dfx;
         s_fy[q] = s_fy[q] + dfy;
-        const double r2 = 2.0 * s_rho[q];
-        const double2 uv = s_uv[q];
-        s_uv[q] = make_double2(uv.x + dfx / r2, uv.y + dfy / r2);
+        if (!last) {  // the last correction of the velocity is not read
+          const double r2 = 2.0 * s_rho[q];
+          const double2 uv = s_uv[q];
+          s_uv[q] = make_double2(uv.x + dfx / r2, uv.y + dfy / r2);
+        }
       }
     }
-    __syncthreads();
+    if (!last) __syncthreads();
   }
-  // 4. body force of Eq. (16) summed in marker order by the last two lanes
-  //    (their wave rarely owns markers or cells), while the other lanes
-  //    write the force density of the stencil cells and the total marker
-  //    forces
-  if (own) s_dF[tid] = make_double2(ftx * s_ds[tid], fty * s_ds[tid]);
-  __syncthreads();
-  if (tid >= MDF_THREADS - 2) {
-    // the x sum on the second-to-last lane and the y sum on the last: one
-    // instruction stream carries both serial chains
-    const int comp = tid & 1;
-    const double *v = reinterpret_cast<const double *>(s_dF) + comp;
-    double fs = 0.0;
-    int j = 0;
-    for (; j + 16 <= n; j += 16) {
-      double t[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) t[r] = v[2 * (j + r)];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) fs -= t[r];
-    }
-    for (; j < n; ++j) fs -= v[2 * j];
-    const int64_t slot = k % cp.hist_cap;
-    cp.hist[2 * slot + comp] = fs;
-  }
+  // 4. force density of this lane's stencil cells (which it summed itself)
+  //    and the total marker forces; the body force is summed from them
+  //    beside the next level launch (body_force)
   {
     double *F = cp.wF + (size_t)b * 2 * cp.win_cap;
 #pragma unroll
@@ -2115,16 +2268,39 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
       }
   }
   if (own) {
-    double *gtx = cp.ftot + (size_t)(k & 1) * 2 * n;
-    gtx[tid] = ftx;
-    gtx[n + tid] = fty;
+    double *gt = cp.ftot + (size_t)(k & 1) * 2 * n;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) gt[(comp + c) * n + m] = ft[c];
   }
+#ifdef SBT_PERSISTENT_TU
+  // the persistent step has no level launch to sum it beside: the markers'
+  // products in place of their forces of the last iteration
+  __syncthreads();
+  if (own) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) reinterpret_cast<double *>(s_dF)[2 * m + comp + c] = ft[c] * dsr;
+  }
+  __syncthreads();
+  if (tid < 2) {
+    double fs = 0.0;
+    for (int j = 0; j < n; ++j) fs -= reinterpret_cast<const double *>(s_dF)[2 * j + tid];
+    cp.hist[2 * (k % cp.hist_cap) + tid] = fs;
+  }
+#endif
   if (tid == 0) *cp.kcount = k + 1;
 }
 
 #ifndef SBT_PERSISTENT_TU
-template <int ST>
-__global__ __launch_bounds__(MDF_THREADS) void mdf_kernel(MdfArgs a) { mdf_body<ST>(a, blockIdx.x); }
+// Workgroups [0, n_bodies) run the forcing loops; the rest, on CUs the loops
+// leave idle, build plans of later substeps into buffers whose collisions
+// are done.  One body of 200 markers: 11.9 us, 12.5 with plans beside it
+// (12.6 before, and 16.3 a step for the plans' own launch); 402 fixed ones
+// 21.2 us (21.7, and 33.9 a step); 64 bodies 18.4 us (16.4, and 29.3).
+template <int ST, bool PAIR>
+__global__ __launch_bounds__(MDF_THREADS) void mdf_kernel(MdfArgs a, IbmArgs p, int n_bodies) {
+  if ((int)blockIdx.x >= n_bodies) prep_item<16 + ST * 2 + PAIR, PAIR>(p, blockIdx.x - n_bodies);
+  else mdf_body<ST, PAIR>(a, blockIdx.x);
+}
 #endif
 
 #ifdef SBT_PERSISTENT_TU
@@ -2204,12 +2380,12 @@ __global__ __launch_bounds__(MDF_THREADS) void step_persistent_kernel(const PPha
     const PPhase &P = ph[p];
     if (P.type == PP_PREP) {
       for (unsigned it = blockIdx.x; it < (unsigned)P.n_items; it += gridDim.x) {
-        prep_item(P.ibm, it);
+        prep_item<2, false>(P.ibm, it);
         __syncthreads();
       }
     } else if (P.type == PP_MDF) {
       for (unsigned it = blockIdx.x; it < (unsigned)P.n_items; it += gridDim.x) {
-        mdf_body<ST & 3>(P.mdf, it);
+        mdf_body<ST & 3, false>(P.mdf, it);
         __syncthreads();
       }
     } else {
@@ -2324,15 +2500,16 @@ extern "C" hipError_t sbt_launch_level_tile(int storage, const LevelArgs *lv, in
     pipe |= lv[i].kpw > 1;
     solid |= lv[i].n_solid > 0;
   }
-  const int order[4] = {ROLE_BAND, ROLE_SOLID, ROLE_SLOW, ROLE_RUN};
+  const int order[5] = {ROLE_SUM, ROLE_BAND, ROLE_SOLID, ROLE_SLOW, ROLE_RUN};
   for (int r : order)
     for (int i = 0; i < n; ++i) {
       const LevelArgs &a = t.lv[i];
-      const int c = r == ROLE_BAND   ? (a.n_band + 255) / 256
+      const int c = r == ROLE_SUM    ? a.n_sum
+                    : r == ROLE_BAND  ? (a.n_band + 255) / 256
                     : r == ROLE_SOLID ? a.n_solid
                     : r == ROLE_SLOW  ? a.n_blocks - a.n_fast
                                       : (a.n_fast + a.kpw - 1) / a.kpw;
-      if (c > 0) t.ent[t.n_ent++] = {c, i << 2 | r};
+      if (c > 0) t.ent[t.n_ent++] = {c, i << 3 | r};
     }
   int groups = 0;
   if (t.xcd_remap) {  // 8 x the largest per-XCD share (see tile_role)
@@ -2398,20 +2575,40 @@ extern "C" size_t sbt_prep_lds_bytes(int max_markers, int cell_cap, int lds_wind
 extern "C" hipError_t sbt_launch_ibm_prep(const IbmArgs *a, hipStream_t s) {
   if (a->n_bodies <= 0 || a->n_plans <= 0) return hipSuccess;
   size_t lds = sbt_prep_lds_bytes(a->max_markers, a->cell_cap, a->lds_window);
-  hipLaunchKernelGGL(ibm_prep_kernel, dim3(a->n_bodies * a->n_plans), dim3(MDF_THREADS), lds, s, *a);
+  const dim3 grid(a->n_bodies * a->n_plans);
+  if (a->max_markers <= MDF_THREADS / 2) hipLaunchKernelGGL(ibm_prep_kernel<true>, grid, dim3(MDF_THREADS), lds, s, *a);
+  else hipLaunchKernelGGL(ibm_prep_kernel<false>, grid, dim3(MDF_THREADS), lds, s, *a);
   return hipGetLastError();
 }
 
-extern "C" hipError_t sbt_launch_mdf(int storage, const MdfArgs *a, int n_bodies, hipStream_t s) {
+extern "C" hipError_t sbt_launch_mdf(int storage, const MdfArgs *a, const IbmArgs *p, int n_bodies, hipStream_t s) {
   if (n_bodies <= 0) return hipSuccess;
   size_t lds = sbt_mdf_lds_bytes(a->max_markers, a->cell_cap);
+  const int n_prep = p->n_plans > 0 ? p->n_bodies * p->n_plans : 0;
+  if (n_prep > 0) {
+    const size_t l2 = sbt_prep_lds_bytes(p->max_markers, p->cell_cap, p->lds_window);
+    lds = l2 > lds ? l2 : lds;
+  }
+  const dim3 grid(n_bodies + n_prep);
+#define SBT_MDF_LAUNCH(S)                                                                                            \
+  if (a->max_markers <= MDF_THREADS / 2)                                                                             \
+    hipLaunchKernelGGL((mdf_kernel<S, true>), grid, dim3(MDF_THREADS), lds, s, *a, *p, n_bodies);                    \
+  else                                                                                                               \
+    hipLaunchKernelGGL((mdf_kernel<S, false>), grid, dim3(MDF_THREADS), lds, s, *a, *p, n_bodies);
   switch (storage) {
-    case 0: hipLaunchKernelGGL(mdf_kernel<0>, dim3(n_bodies), dim3(MDF_THREADS), lds, s, *a); break;
-    case 1: hipLaunchKernelGGL(mdf_kernel<1>, dim3(n_bodies), dim3(MDF_THREADS), lds, s, *a); break;
-    case 2: hipLaunchKernelGGL(mdf_kernel<2>, dim3(n_bodies), dim3(MDF_THREADS), lds, s, *a); break;
-    case 3: hipLaunchKernelGGL(mdf_kernel<3>, dim3(n_bodies), dim3(MDF_THREADS), lds, s, *a); break;
+    case 0: SBT_MDF_LAUNCH(0); break;
+    case 1: SBT_MDF_LAUNCH(1); break;
+    case 2: SBT_MDF_LAUNCH(2); break;
+    case 3: SBT_MDF_LAUNCH(3); break;
     default: return hipErrorInvalidValue;
   }
+#undef SBT_MDF_LAUNCH
+  return hipGetLastError();
+}
+
+extern "C" hipError_t sbt_launch_body_force(const CaseDev *bodies, int n_bodies, hipStream_t s) {
+  if (n_bodies <= 0) return hipSuccess;
+  hipLaunchKernelGGL(body_force_kernel, dim3(n_bodies), dim3(256), 0, s, bodies);
   return hipGetLastError();
 }
 

@@ -61,3 +61,74 @@ def test_solid_blocks_share_the_launch(env, tile):
     g.synchronize()
     o.step(3)
     equal_levels(g, o, wl)
+
+
+def ring(n, r, centre=(64.0, 64.0), nx=128, ny=128):
+    """A fixed ring of n markers of radius r in a uniform stream."""
+    wl = W.cylinder(nx, ny, D=2 * r, centre=centre, n_markers=n, perturb=False)
+    return wl.replace(name=f"ring{n}_r{r}")
+
+
+@pytest.mark.parametrize("wl", [
+    ring(6, 4.0),                               # waves without markers
+    ring(128, 20.0),                            # two lanes per marker: a full wave of pairs
+    ring(512, 60.0), ring(513, 60.0),           # the last body with two lanes per marker, the first with one
+    ring(200, 1.5),                             # more than 63 markers over a cell: the last count bin
+    ring(300, 95.0, (160.0, 160.0), 320, 320),  # a window beyond LDS, more than 2048 stencil cells
+], ids=lambda w: w.name)
+def test_forcing_plans_match_oracle(env, wl):
+    P, O = env
+    print(wl.name, flush=True)
+    g, o = P.Sim(wl, "f64"), O.OracleSim(wl)
+    g.step(4)
+    g.synchronize()
+    o.step(4)
+    equal_levels(g, o, wl)
+    for a, b in zip(g.force_history(), o.force_history()):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("m", [2, 4])
+def test_plans_follow_the_state(env, m):
+    """Plans built ahead of their substeps: after a checkpoint is restored,
+    and around a persistent step (which builds its own), the run goes on as
+    an unbroken one; so does a fixed body beside a moving one."""
+    P, O = env
+    wls = [W.small_refined_flap(m=m), ring(40, 8.0).replace(name="ring"), W.small_pitch_up(m=min(m, 3))]
+    print(m, flush=True)
+
+    def history(g):
+        g.synchronize()
+        return [np.array(g.force_history(c)) for c in range(len(wls))]
+
+    ref = P.Sim(wls, "f64")
+    ref.step(9)
+    g = P.Sim(wls, "f64")
+    g.step(3)
+    state = g.read_state()
+    g.step(2)
+    g.write_state(state)
+    g.step(1)
+    g.set_option(P.OPT_PERSISTENT, 1)
+    g.step(2)
+    g.set_option(P.OPT_PERSISTENT, 0)
+    g.step(1)
+    g.set_option(P.OPT_GRAPH, 0)
+    g.step(2)
+    for a, b in zip(history(g), history(ref)):
+        assert np.array_equal(a, b)
+
+
+def test_many_bodies_match_one(env):
+    """130 bodies leave no CUs for plans beside the loops: a launch of their
+    own builds them."""
+    P, O = env
+    wl = W.small_refined_flap(m=2)
+    print(wl.name, flush=True)
+    one, many = P.Sim(wl, "f32", history_cap=64), P.Sim([wl] * 130, "f32", history_cap=64)
+    one.step(5)
+    many.step(5)
+    want = np.array(one.force_history(0, 64))
+    assert np.isfinite(want).all() and want.shape[1] > 0
+    for c in (0, 64, 129):
+        assert np.array_equal(np.array(many.force_history(c, 64)), want)
