@@ -299,10 +299,10 @@ struct Ibm3 {
   double *phi;                 // [12][n] the 4 weights per axis (x, y, z)
   double *ud;                  // [3][n] desired velocity r(t + 1) - r(t)
   double *rho, *u;             // [K], [3][K] box moments
-  double *g, *ft;              // [3][n] force of the pass, total force per marker
+  double *g, *ft;              // [3][n] force of the pass, total force per marker; before the first
+                               // pass g holds the marker kernel's tap bounds, [workgroup][6] ints
   double *Fbox;                // [3][K] force density the step kernel adds
   int *box;                    // [6] the box: origin and size (size 0: no force this step)
-  int *lohi;                   // [6] tap bounds reduced over the markers
   double *fs;                  // [2][3] F_s of forcing loop L in slot L & 1
   int *err;                    // bit 2: the box outgrew cap or left the lattice
 };
@@ -338,116 +338,136 @@ Pose3 pose3(const Ibm3 &b, double t) {
   return q;
 }
 
-__device__ __forceinline__ void marker3(const Ibm3 &b, const Pose3 &q, int j, double &X, double &Y, double &Z) {
+__device__ __forceinline__ double marker3(const Ibm3 &b, const Pose3 &q, int j, int axis) {
 #pragma clang fp contract(off)
-  if (b.kind == 0) {
-    X = b.xb[j];
-    Y = b.yb[j];
-    Z = b.zb[j];
-    return;
-  }
-  X = b.mp[0] + b.xb[j] * q.ca + b.zb[j] * q.sa;
-  Y = b.mp[1] + b.yb[j];
-  Z = q.zc - b.xb[j] * q.sa + b.zb[j] * q.ca;
+  if (b.kind == 0) return axis == 0 ? b.xb[j] : (axis == 1 ? b.yb[j] : b.zb[j]);
+  if (axis == 0) return b.mp[0] + b.xb[j] * q.ca + b.zb[j] * q.sa;
+  if (axis == 1) return b.mp[1] + b.yb[j];
+  return q.zc - b.xb[j] * q.sa + b.zb[j] * q.ca;
 }
 
 __device__ __forceinline__ long long box_cells(const int *B) { return (long long)B[3] * B[4] * B[5]; }
 
 // Sec. 2.2 in 3D, the forcing loop before the collision of step t, as a
 // chain of launches on the stream: ibm3_markers_kernel (markers, desired
-// velocities, 4x4x4 taps with weight phi_x (phi_y phi_z)), ibm3_box_kernel
-// (the box they cover; it also resets the bounds for the next loop),
-// ibm3_moments_kernel (rho, u of the box cells from
-// the state the step collides), then N_F times ibm3_interp_kernel (U_j,
+// velocities, 4x4x4 taps with weight phi_x (phi_y phi_z); once for a body at
+// rest), ibm3_moments_kernel (the box they cover and rho, u of its cells
+// from the state the step collides), then N_F times ibm3_interp_kernel (U_j,
 // rho_j over the taps, z outer, y, x inner; g_j = 2 rho_j (u_d - U_j)) and
 // ibm3_spread_kernel (each box cell sums g_j phi dA_j over the markers in
-// marker order, then F += dF, u += dF / (2 rho)).  The loop's body force F_s is summed by the first
-// workgroup of the step kernel that follows it.
-// Marker j at step t: position, desired velocity, taps and weights; clears
-// its force total; the workgroup's tap bounds go into lohi.
+// marker order, then F += dF, u += dF / (2 rho)).  The loop's body force F_s
+// is summed by the first workgroup of the step kernel that follows it.  Each
+// launch is bound by its own chain of memory and FP64 latencies, so the work
+// of a marker is spread over lanes wherever the order of a sum allows it.
+// Loop of an ellipsoid of 1200 markers in 128^3, us, before -> now: markers
+// 16.8 -> 5.2, box 4.6 -> in the moments, moments 5.1 -> 6.7, interpolation
+// 3 x 14.2 -> 3 x 5.1, spreading 3 x 30.2 -> 3 x 11.9; in all 160 -> 63.
+
+// Markers of step t, 16 lanes each: lane (axis, k) finds one weight; lane
+// (axis, 0) position, desired velocity and first tap.  The workgroup's tap
+// bounds go into its row of g.
+constexpr int kMkLanes = 16, kMkPer = kThreads / kMkLanes;  // lanes per marker, markers per workgroup
+
 __global__ __launch_bounds__(kThreads) void ibm3_markers_kernel(Pose3 q0, Pose3 q1, Ibm3 b) {
 #pragma clang fp contract(off)
-  __shared__ int s_lo[3], s_hi[3];
-  const int tid = threadIdx.x, n = b.n, j = blockIdx.x * blockDim.x + tid;
-  if (tid < 3) {
-    s_lo[tid] = 1 << 30;
-    s_hi[tid] = -(1 << 30);
-  }
-  __syncthreads();
-  if (j < n) {
-    double X, Y, Z, X1, Y1, Z1;
-    marker3(b, q0, j, X, Y, Z);
-    if (b.kind == 0) {
-      X1 = X;
-      Y1 = Y;
-      Z1 = Z;
-    } else {
-      marker3(b, q1, j, X1, Y1, Z1);
+  __shared__ int s_lo[3][kMkPer], s_hi[3][kMkPer];
+  const int tid = threadIdx.x, n = b.n, w = tid / kMkLanes, j = blockIdx.x * kMkPer + w;
+  const int a = (tid >> 2) & 3, k = tid & 3;
+  if (a < 3) {
+    int lo = 1 << 30, hi = -(1 << 30);
+    if (j < n) {
+      const double P = marker3(b, q0, j, a);
+      const int t0 = (int)floor(P - 1.5);
+      b.phi[(a * 4 + k) * n + j] = peskin3d(t0 + k + 0.5 - P);
+      if (k == 0) {
+        b.ud[a * n + j] = b.kind == 0 ? 0.0 : marker3(b, q1, j, a) - P;
+        b.tap[a * n + j] = t0;
+      }
+      lo = t0;
+      hi = t0 + 4;
     }
-    b.ud[j] = X1 - X;
-    b.ud[n + j] = Y1 - Y;
-    b.ud[2 * n + j] = Z1 - Z;
-    b.ft[j] = b.ft[n + j] = b.ft[2 * n + j] = 0.0;
-    const double P[3] = {X, Y, Z};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int t0 = (int)floor(P[a] - 1.5);
-      b.tap[a * n + j] = t0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) b.phi[(a * 4 + k) * n + j] = peskin3d(t0 + k + 0.5 - P[a]);
-      atomicMin(&s_lo[a], t0);
-      atomicMax(&s_hi[a], t0 + 4);
+    if (k == 0) {
+      s_lo[a][w] = lo;
+      s_hi[a][w] = hi;
     }
   }
   __syncthreads();
-  if (tid < 3) {
-    atomicMin(&b.lohi[tid], s_lo[tid]);
-    atomicMax(&b.lohi[3 + tid], s_hi[tid]);
+  if (tid < 6) {
+    const int ax = tid % 3;
+    int v = tid < 3 ? s_lo[ax][0] : s_hi[ax][0];
+    for (int i = 1; i < kMkPer; ++i) v = tid < 3 ? min(v, s_lo[ax][i]) : max(v, s_hi[ax][i]);
+    reinterpret_cast<int *>(b.g)[blockIdx.x * 6 + tid] = v;
   }
 }
 
-// The box of this loop from the reduced bounds; a box outside the lattice
-// or above cap gives no force this step (the host reports it at the next
-// synchronisation).
-__global__ __launch_bounds__(64) void ibm3_box_kernel(Params p, Ibm3 b) {
-  if (threadIdx.x != 0) return;
+// The box of this loop from the marker kernel's `rows` bounds, found by every
+// workgroup for itself; a box outside the lattice or above cap gives no
+// force this step (the host reports it at the next synchronisation).
+__device__ __forceinline__ void find_box(const Params &p, const Ibm3 &b, int rows, int box[6]) {
+  __shared__ int s_v[6][kThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int v[6] = {1 << 30, 1 << 30, 1 << 30, -(1 << 30), -(1 << 30), -(1 << 30)};
+  const int *rw = reinterpret_cast<const int *>(b.g);
+  for (int i = tid; i < rows; i += kThreads)
+#pragma unroll
+    for (int a = 0; a < 6; ++a) v[a] = a < 3 ? min(v[a], rw[i * 6 + a]) : max(v[a], rw[i * 6 + a]);
+#pragma unroll
+  for (int a = 0; a < 6; ++a) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const int u = __shfl_xor(v[a], o, 64);
+      v[a] = a < 3 ? min(v[a], u) : max(v[a], u);
+    }
+    if (lane == 0) s_v[a][wave] = v[a];
+  }
+  __syncthreads();
   const int dims[3] = {p.nx, p.ny, p.nz};
   long long K = 1;
   bool bad = false;
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const int lo = b.lohi[a], hi = b.lohi[3 + a];
-    K *= hi - lo;
-    bad |= lo < 0 || hi > dims[a];
+  for (int a = 0; a < 6; ++a) {
+    v[a] = s_v[a][0];
+    for (int w = 1; w < kThreads / 64; ++w) v[a] = a < 3 ? min(v[a], s_v[a][w]) : max(v[a], s_v[a][w]);
   }
-  int box[6] = {0, 0, 0, 0, 0, 0};
-  if (bad || K > b.cap) {
-    atomicOr(b.err, 2);
-  } else {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      box[a] = b.lohi[a];
-      box[3 + a] = b.lohi[3 + a] - b.lohi[a];
+  for (int a = 0; a < 3; ++a) {
+    K *= v[3 + a] - v[a];
+    bad |= v[a] < 0 || v[3 + a] > dims[a];
+  }
+  bad |= K > b.cap;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    box[a] = bad ? 0 : v[a];
+    box[3 + a] = bad ? 0 : v[3 + a] - v[a];
+  }
+  if (blockIdx.x == 0) {
+    if (tid == 0 && bad) atomicOr(b.err, 2);
+    if (tid < 6) {
+      int o = box[0];
+#pragma unroll
+      for (int a = 1; a < 6; ++a) o = tid == a ? box[a] : o;
+      b.box[tid] = o;
     }
-  }
-#pragma unroll
-  for (int a = 0; a < 6; ++a) b.box[a] = box[a];
-  // the bounds start over for the next loop's marker kernel
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    b.lohi[a] = 1 << 30;
-    b.lohi[3 + a] = -(1 << 30);
   }
 }
 
-// rho, u of box cell k from the state the next step collides (gathered when
-// the lattice holds post-collision populations); clears the box force.
+// The loop's box (rows > 0: from the marker kernel, else as it is), rho, u of
+// box cell k from the state the next step collides (gathered when the
+// lattice holds post-collision populations); clears the box force and the
+// markers' force totals.
 template <int ST, int kQ3>
-__global__ __launch_bounds__(kThreads) void ibm3_moments_kernel(Params p, const void *lat_, int pull, Ibm3 b) {
+__global__ __launch_bounds__(kThreads) void ibm3_moments_kernel(Params p, const void *lat_, int pull, Ibm3 b, int rows) {
 #pragma clang fp contract(off)
   using S = Store3<ST>;
   using T = typename S::T;
-  const int *B = b.box;
+  int B[6];
+  if (rows > 0) {
+    find_box(p, b, rows, B);
+  } else {
+#pragma unroll
+    for (int a = 0; a < 6; ++a) B[a] = b.box[a];
+  }
+  for (int i = blockIdx.x * kThreads + threadIdx.x; i < 3 * b.n; i += gridDim.x * kThreads) b.ft[i] = 0.0;
   const long long K = box_cells(B), k = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (k >= K) return;
   const T *lat = static_cast<const T *>(lat_);
@@ -471,144 +491,170 @@ __global__ __launch_bounds__(kThreads) void ibm3_moments_kernel(Params p, const 
   b.Fbox[k] = b.Fbox[K + k] = b.Fbox[2 * K + k] = 0.0;
 }
 
-// One pass's interpolation for marker j: U_j, rho_j, g_j; ft_j += g_j.
+// One pass's interpolation: U_j, rho_j, g_j; ft_j += g_j.  A wave forms the
+// 64 products of a marker's taps side by side (4 sums), 4 markers after one
+// another; then one lane per marker and sum adds its 64 in tap order, z
+// outer, y, x inner, from LDS.
+constexpr int kInPer = 16;  // markers per workgroup (4 waves, 4 markers each)
+
 __global__ __launch_bounds__(kThreads) void ibm3_interp_kernel(Ibm3 b) {
 #pragma clang fp contract(off)
+  __shared__ double s_p[4 * kInPer][65];
   const int *B = b.box;
-  const int n = b.n, j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n || B[3] == 0) return;
-  const int bwx = B[3], bwy = B[4];
-  const int i0 = b.tap[j] - B[0], j0 = b.tap[n + j] - B[1], k0 = b.tap[2 * n + j] - B[2];
+  const int n = b.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int bwx = B[3], bwy = B[4], bx = B[0], by = B[1], bz = B[2];
+  if (bwx == 0) return;  // the whole grid: no force this step
   const long long K = box_cells(B);
-  double U0 = 0.0, U1 = 0.0, U2 = 0.0, R = 0.0;
-  for (int cz = 0; cz < 4; ++cz) {
-    const double pz = b.phi[(8 + cz) * n + j];
-    for (int cy = 0; cy < 4; ++cy) {
-      const double pyz = b.phi[(4 + cy) * n + j] * pz;
-      for (int cx = 0; cx < 4; ++cx) {
-        const double w = b.phi[cx * n + j] * pyz;
-        const long long k = ((long long)(k0 + cz) * bwy + (j0 + cy)) * bwx + (i0 + cx);
-        U0 += b.u[k] * w;
-        U1 += b.u[K + k] * w;
-        U2 += b.u[2 * K + k] * w;
-        R += b.rho[k] * w;
-      }
-    }
+  const int cx = lane & 3, cy = (lane >> 2) & 3, cz = lane >> 4;
+  const int j0 = blockIdx.x * kInPer;
+  double v[4][4], w[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int j = min(j0 + wave * 4 + r, n - 1);  // past the last marker: repeated, not used
+    const int x = b.tap[j] - bx + cx, y = b.tap[n + j] - by + cy, z = b.tap[2 * n + j] - bz + cz;
+    const long long k = ((long long)z * bwy + y) * bwx + x;
+    w[r] = b.phi[cx * n + j] * (b.phi[(4 + cy) * n + j] * b.phi[(8 + cz) * n + j]);
+    v[r][0] = b.u[k];
+    v[r][1] = b.u[K + k];
+    v[r][2] = b.u[2 * K + k];
+    v[r][3] = b.rho[k];
   }
-  const double g0 = 2.0 * R * (b.ud[j] - U0), g1 = 2.0 * R * (b.ud[n + j] - U1);
-  const double g2 = 2.0 * R * (b.ud[2 * n + j] - U2);
-  b.g[j] = g0;
-  b.g[n + j] = g1;
-  b.g[2 * n + j] = g2;
-  b.ft[j] += g0;
-  b.ft[n + j] += g1;
-  b.ft[2 * n + j] += g2;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s_p[(wave * 4 + r) * 4 + q][lane] = v[r][q] * w[r];
+  __syncthreads();
+  if (wave > 0) return;
+  // lane = marker * 4 + sum
+  const int j = j0 + (lane >> 2), q = lane & 3;
+  double s = 0.0;
+#pragma unroll
+  for (int t = 0; t < 64; t += 16) {
+    double e[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) e[i] = s_p[lane][t + i];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += e[i];
+  }
+  const double R = __shfl(s, lane | 3, 64);
+  if (j >= n || q == 3) return;
+  const double g = 2.0 * R * (b.ud[q * n + j] - s);
+  b.g[q * n + j] = g;
+  b.ft[q * n + j] += g;
 }
 
 // One pass's spreading, markers in order.  A one-wave workgroup takes 4x4x4
-// tiles of the box (grid-stride).  For each tile it stages the taps of up to
-// kSpBlock markers in LDS at once and lists, in marker order, the markers
-// whose 4x4x4 stencil reaches the tile (no global load in this scan); then
-// it stages the listed markers' weights, g_j and dA_j 64 at a time (one
-// round of loads per 64 listed markers) and each cell sums over them.
+// tiles of the box (grid-stride), one cell per lane.  Per block of kSpBlock
+// markers it lists, in marker order, the markers whose stencil reaches the
+// tile, then stages their weights, g_j and dA_j 64 at a time.  Per axis and
+// tile position a ballot over the staged markers says which of them reach
+// it; the AND of a cell's three is the set it sums over, lowest bit first,
+// so a cell visits its own contributors (one in five of the listed ones on
+// average) and no others.
 constexpr int kSpThreads = 64, kSpTx = 4, kSpTy = 4, kSpTz = kSpThreads / (kSpTx * kSpTy), kSpBlock = 1024;
 static_assert(kSpTz * kSpTx * kSpTy == kSpThreads && kSpThreads == 64, "one wave, one cell per lane");
 
-__global__ __launch_bounds__(kSpThreads) void ibm3_spread_kernel(Ibm3 b) {
+__global__ __launch_bounds__(kSpThreads) void ibm3_spread_kernel(Ibm3 b, int last) {
 #pragma clang fp contract(off)
-  __shared__ int s_tap[3][kSpBlock];
-  __shared__ int s_rel[kSpBlock];
-  __shared__ int s_t[3][kSpThreads];
+  __shared__ uint16_t s_rel[kSpBlock];
+  __shared__ int s_t[kSpThreads];          // first tap relative to the tile, 3 x 8 bits
   __shared__ double s_phi[12][kSpThreads];
-  __shared__ double s_g[3][kSpThreads];
-  __shared__ double s_dA[kSpThreads];
+  __shared__ double s_g[4][kSpThreads];    // g_x, g_y, g_z, dA
   const int *B = b.box;
   const int lane = threadIdx.x, n = b.n;
-  const int bwx = B[3], bwy = B[4], bwz = B[5];
+  const int bwx = B[3], bwy = B[4], bwz = B[5], bx = B[0], by = B[1], bz = B[2];
   if (bwx == 0) return;  // the whole grid: no force this step
   const long long K = box_cells(B);
   const int ntx = (bwx + kSpTx - 1) / kSpTx, nty = (bwy + kSpTy - 1) / kSpTy, ntz = (bwz + kSpTz - 1) / kSpTz;
   const int tiles = ntx * nty * ntz;
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int xlo = (tile % ntx) * kSpTx, ylo = ((tile / ntx) % nty) * kSpTy, zlo = (tile / (ntx * nty)) * kSpTz;
-    const int xhi = min(xlo + kSpTx, bwx) - 1, yhi = min(ylo + kSpTy, bwy) - 1, zhi = min(zlo + kSpTz, bwz) - 1;
-    const int x = xlo + lane % kSpTx, y = ylo + (lane / kSpTx) % kSpTy, z = zlo + lane / (kSpTx * kSpTy);
-    const bool live = x <= xhi && y <= yhi && z <= zhi;
+    const int lx = lane % kSpTx, ly = (lane / kSpTx) % kSpTy, lz = lane / (kSpTx * kSpTy);
+    const bool live = xlo + lx < bwx && ylo + ly < bwy && zlo + lz < bwz;
     double d0 = 0.0, d1 = 0.0, d2 = 0.0;
     for (int b0 = 0; b0 < n; b0 += kSpBlock) {
       const int bn = min(kSpBlock, n - b0);
-      {  // taps in the box frame: all loads issued before the LDS stores
-        constexpr int kPer = kSpBlock / kSpThreads;
-        int v[3][kPer];
-#pragma unroll
-        for (int r = 0; r < kPer; ++r) {
-          const int i = r * kSpThreads + lane;
-#pragma unroll
-          for (int a = 0; a < 3; ++a) v[a][r] = i < bn ? b.tap[a * n + b0 + i] : 0;
-        }
-#pragma unroll
-        for (int r = 0; r < kPer; ++r) {
-          const int i = r * kSpThreads + lane;
-#pragma unroll
-          for (int a = 0; a < 3; ++a) s_tap[a][i] = v[a][r] - B[a];
-        }
-      }
-      __syncthreads();
-      // the markers of this block that reach the tile, in marker order
+      // the markers of this block that reach the tile, in marker order (a
+      // marker's first tap lies at most 3 cells before a cell it reaches)
       int cnt = 0;
-      for (int c0 = 0; c0 < bn; c0 += kSpThreads) {
-        const int i = c0 + lane;
-        bool f = false;
-        if (i < bn) {
-          const int tx = s_tap[0][i], ty = s_tap[1][i], tz = s_tap[2][i];
-          f = tx <= xhi && tx + 3 >= xlo && ty <= yhi && ty + 3 >= ylo && tz <= zhi && tz + 3 >= zlo;
+      for (int c0 = 0; c0 < bn; c0 += 4 * kSpThreads) {
+        int tx[4], ty[4], tz[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int j = b0 + min(c0 + r * kSpThreads + lane, bn - 1);
+          tx[r] = b.tap[j] - bx - xlo;
+          ty[r] = b.tap[n + j] - by - ylo;
+          tz[r] = b.tap[2 * n + j] - bz - zlo;
         }
-        const unsigned long long m = __ballot(f);
-        if (f) s_rel[cnt + __popcll(m & ((1ull << lane) - 1ull))] = i;
-        cnt += __popcll(m);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = c0 + r * kSpThreads + lane;
+          const bool f = i < bn && (unsigned)(tx[r] + 3) <= 6u && (unsigned)(ty[r] + 3) <= 6u && (unsigned)(tz[r] + 3) <= 6u;
+          const unsigned long long m = __ballot(f);
+          if (f) s_rel[cnt + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)i;
+          cnt += __popcll(m);
+        }
       }
       __syncthreads();
       for (int g0 = 0; g0 < cnt; g0 += kSpThreads) {
-        const int total = min(kSpThreads, cnt - g0);
-        if (lane < total) {
-          const int i = s_rel[g0 + lane], jc = b0 + i;
-          s_t[0][lane] = s_tap[0][i];
-          s_t[1][lane] = s_tap[1][i];
-          s_t[2][lane] = s_tap[2][i];
-          double w[12], gg[3];
+        const bool has = lane < min(kSpThreads, cnt - g0);
+        int t[3] = {64, 64, 64};  // reaches no cell
+        if (has) {
+          const int j = b0 + s_rel[g0 + lane];
+          double w[12], gg[4];
 #pragma unroll
-          for (int q = 0; q < 12; ++q) w[q] = b.phi[q * n + jc];
+          for (int q = 0; q < 12; ++q) w[q] = b.phi[q * n + j];
 #pragma unroll
-          for (int a = 0; a < 3; ++a) gg[a] = b.g[a * n + jc];
-          const double dA = b.dA[jc];
+          for (int a = 0; a < 3; ++a) gg[a] = b.g[a * n + j];
+          gg[3] = b.dA[j];
+          t[0] = b.tap[j] - bx - xlo;
+          t[1] = b.tap[n + j] - by - ylo;
+          t[2] = b.tap[2 * n + j] - bz - zlo;
 #pragma unroll
           for (int q = 0; q < 12; ++q) s_phi[q][lane] = w[q];
 #pragma unroll
-          for (int a = 0; a < 3; ++a) s_g[a][lane] = gg[a];
-          s_dA[lane] = dA;
+          for (int q = 0; q < 4; ++q) s_g[q][lane] = gg[q];
+          s_t[lane] = (t[0] & 255) | (t[1] & 255) << 8 | (t[2] & 255) << 16;
         }
-        __syncthreads();
-        if (live) {
-          for (int c = 0; c < total; ++c) {
-            const int dx = x - s_t[0][c], dy = y - s_t[1][c], dz = z - s_t[2][c];
-            if ((unsigned)dx > 3u || (unsigned)dy > 3u || (unsigned)dz > 3u) continue;
-            const double w = s_phi[dx][c] * (s_phi[4 + dy][c] * s_phi[8 + dz][c]);
-            d0 += s_g[0][c] * w * s_dA[c];
-            d1 += s_g[1][c] * w * s_dA[c];
-            d2 += s_g[2][c] * w * s_dA[c];
+        const int l3[3] = {lx, ly, lz};
+        unsigned long long mine = ~0ull;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          unsigned long long at = 0ull;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const unsigned long long m = __ballot((unsigned)(q - t[a]) <= 3u);
+            at = l3[a] == q ? m : at;
           }
+          mine &= at;
+        }
+        if (!live) mine = 0ull;
+        __syncthreads();
+        while (mine) {
+          const int c = __builtin_ctzll(mine);
+          mine &= mine - 1ull;
+          const int tt = s_t[c];
+          const int dx = lx - (int)(int8_t)tt, dy = ly - (int)(int8_t)(tt >> 8), dz = lz - (int)(int8_t)(tt >> 16);
+          const double w = s_phi[dx][c] * (s_phi[4 + dy][c] * s_phi[8 + dz][c]);
+          const double dA = s_g[3][c];
+          d0 += s_g[0][c] * w * dA;
+          d1 += s_g[1][c] * w * dA;
+          d2 += s_g[2][c] * w * dA;
         }
         __syncthreads();  // the group is restaged by the next one
       }
     }
     if (!live || (d0 == 0.0 && d1 == 0.0 && d2 == 0.0)) continue;
-    const long long k = ((long long)z * bwy + y) * bwx + x;
+    const long long k = ((long long)(zlo + lz) * bwy + ylo + ly) * bwx + xlo + lx;
     b.Fbox[k] += d0;
     b.Fbox[K + k] += d1;
     b.Fbox[2 * K + k] += d2;
-    b.u[k] += d0 / (2.0 * b.rho[k]);
-    b.u[K + k] += d1 / (2.0 * b.rho[k]);
-    b.u[2 * K + k] += d2 / (2.0 * b.rho[k]);
+    if (!last) {  // the last correction of the velocity is not read
+      const double r2 = 2.0 * b.rho[k];
+      b.u[k] += d0 / r2;
+      b.u[K + k] += d1 / r2;
+      b.u[2 * K + k] += d2 / r2;
+    }
   }
 }
 
@@ -843,7 +889,7 @@ sbt3_desc with_box(sbt3_desc d) {
 size_t body_bytes(const sbt3_desc *d) {
   const size_t n = d->n_markers, cap = (size_t)d->ibm_box_cells;
   return 4 * align256(n * 8) + align256(3 * n * 4) + align256(12 * n * 8) + 3 * align256(3 * n * 8) +
-         align256(cap * 8) + 2 * align256(3 * cap * 8) + 2 * align256(6 * 4) + align256(6 * 8) + align256(4);
+         align256(cap * 8) + 2 * align256(3 * cap * 8) + align256(6 * 4) + align256(6 * 8) + align256(4);
 }
 
 size_t plan_bytes(const sbt3_desc *d, long long *stage, long long records) {
@@ -882,31 +928,24 @@ size_t plan_bytes(const sbt3_desc *d, long long *stage, long long records) {
 
 hipError_t launch_ibm(sbt3_ctx &X, int pull) {
   const Ibm3 &B = X.ibm;
-  // one wave per workgroup for the per-marker kernels: their threads are
-  // few and latency-bound, so they are spread over as many CUs as possible
-  const dim3 gk((unsigned)((B.cap + kThreads - 1) / kThreads)), gn((unsigned)((B.n + 63) / 64));
-  // tiles, grid-stride: the box is known only on the device and is mostly
+  const dim3 gk((unsigned)((B.cap + kThreads - 1) / kThreads)), gi((unsigned)((B.n + kInPer - 1) / kInPer));
+  // tiles, grid-stride: the box is known only on the device and may be
   // smaller than cap, and workgroups that find no tile still cost dispatch
-  // time, so the grid is capped at two small workgroups per CU
-  const dim3 gs((unsigned)std::min<long long>(512, (B.cap + kSpThreads - 1) / kSpThreads));
-  const Pose3 q0 = B.kind ? pose3(B, (double)X.ibm_t) : Pose3{}, q1 = B.kind ? pose3(B, (double)(X.ibm_t + 1)) : Pose3{};
-  hipLaunchKernelGGL(ibm3_markers_kernel, gn, dim3(64), 0, X.stream, q0, q1, B);
-  hipLaunchKernelGGL(ibm3_box_kernel, dim3(1), dim3(64), 0, X.stream, X.p, B);
-  const void *lat = X.lat[X.cur];
-  switch (X.d.storage + 4 * (X.d.lattice == 27)) {
-    case 0: hipLaunchKernelGGL((ibm3_moments_kernel<0, 19>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    case 1: hipLaunchKernelGGL((ibm3_moments_kernel<1, 19>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    case 2: hipLaunchKernelGGL((ibm3_moments_kernel<2, 19>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    case 3: hipLaunchKernelGGL((ibm3_moments_kernel<3, 19>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    case 4: hipLaunchKernelGGL((ibm3_moments_kernel<0, 27>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    case 5: hipLaunchKernelGGL((ibm3_moments_kernel<1, 27>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    case 6: hipLaunchKernelGGL((ibm3_moments_kernel<2, 27>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    case 7: hipLaunchKernelGGL((ibm3_moments_kernel<3, 27>), gk, dim3(kThreads), 0, X.stream, X.p, lat, pull, B); break;
-    default: return hipErrorInvalidValue;
+  // time, so the grid is capped at what the chip holds at once (8 of these
+  // one-wave workgroups on each of 256 CUs)
+  const dim3 gs((unsigned)std::min<long long>(2048, (B.cap + kSpThreads - 1) / kSpThreads));
+  int rows = 0;
+  if (B.kind != 0 || X.ibm_t == 0) {  // a body at rest keeps its markers and box
+    const Pose3 q0 = B.kind ? pose3(B, (double)X.ibm_t) : Pose3{}, q1 = B.kind ? pose3(B, (double)(X.ibm_t + 1)) : Pose3{};
+    rows = (B.n + kMkPer - 1) / kMkPer;
+    hipLaunchKernelGGL(ibm3_markers_kernel, dim3((unsigned)rows), dim3(kThreads), 0, X.stream, q0, q1, B);
   }
+  const void *lat = X.lat[X.cur];
+  hipError_t e = SBT3_LAUNCH(ibm3_moments_kernel, X.d.storage, X.d.lattice, gk, X.stream, X.p, lat, pull, B, rows);
+  if (e != hipSuccess) return e;
   for (int it = 0; it < B.iters; ++it) {
-    hipLaunchKernelGGL(ibm3_interp_kernel, gn, dim3(64), 0, X.stream, B);
-    hipLaunchKernelGGL(ibm3_spread_kernel, gs, dim3(kSpThreads), 0, X.stream, B);
+    hipLaunchKernelGGL(ibm3_interp_kernel, gi, dim3(kThreads), 0, X.stream, B);
+    hipLaunchKernelGGL(ibm3_spread_kernel, gs, dim3(kSpThreads), 0, X.stream, B, it + 1 == B.iters ? 1 : 0);
   }
   return hipGetLastError();
 }
@@ -1050,7 +1089,6 @@ sbt_status sbt3_create(const sbt3_desc *desc_in, void *device_buf, size_t bytes,
     B.u = reinterpret_cast<double *>(take(3 * cap * 8));
     B.Fbox = reinterpret_cast<double *>(take(3 * cap * 8));
     B.box = reinterpret_cast<int *>(take(6 * 4));
-    B.lohi = reinterpret_cast<int *>(take(6 * 4));
     B.fs = reinterpret_cast<double *>(take(6 * 8));
     B.err = X->err;
     bool ok = hipMemcpy(xb, desc->marker_xyz, n * 8, hipMemcpyHostToDevice) == hipSuccess;
@@ -1059,8 +1097,6 @@ sbt_status sbt3_create(const sbt3_desc *desc_in, void *device_buf, size_t bytes,
     ok &= hipMemcpy(dA, desc->marker_dA, n * 8, hipMemcpyHostToDevice) == hipSuccess;
     ok &= hipMemset(B.box, 0, 6 * 4) == hipSuccess;
     ok &= hipMemset(B.fs, 0, 6 * 8) == hipSuccess;
-    const int lohi0[6] = {1 << 30, 1 << 30, 1 << 30, -(1 << 30), -(1 << 30), -(1 << 30)};
-    ok &= hipMemcpy(B.lohi, lohi0, sizeof lohi0, hipMemcpyHostToDevice) == hipSuccess;
     ok &= hipMemset(B.ft, 0, 3 * n * 8) == hipSuccess;
     if (!ok) {
       delete X;

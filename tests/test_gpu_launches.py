@@ -132,3 +132,26 @@ def test_many_bodies_match_one(env):
     assert np.isfinite(want).all() and want.shape[1] > 0
     for c in (0, 64, 129):
         assert np.array_equal(np.array(many.force_history(c, 64)), want)
+
+
+def marker_box(n, moving):
+    """n markers on a small sphere (or a pitching, plunging ellipsoid)."""
+    if moving:
+        return W.flapping_ellipsoid3(n=32, chord=12.0, n_markers=n)
+    return W.ibm_sphere3(n=24, r=4.0, n_markers=n, g=1e-6)
+
+
+@pytest.mark.parametrize("n,moving", [(1, False), (16, True), (17, False), (65, True), (1024, False), (1025, True)])
+def test_forcing_loop3_matches_oracle(env, n, moving):
+    """Marker counts around a workgroup's 16, a wave's 64 and a block's 1024."""
+    P, O = env
+    wl = marker_box(n, moving)
+    print(wl.name, n, flush=True)
+    g, o = P.Sim3(wl, "f64"), O.Oracle3Sim(wl)
+    for _ in range(2):
+        g.step(2)
+        g.synchronize()
+        o.step(2)
+        assert np.array_equal(g.body_force(), o.body_force())
+    for a, b in zip(g.fields(), o.fields()):
+        assert np.array_equal(a, b)
