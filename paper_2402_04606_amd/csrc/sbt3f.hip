@@ -82,31 +82,12 @@ struct Args3 {
   const int32_t *band;  // halo cells gathered in the launch (block * 512 + cell), after the blocks
   int32_t n_band;
   int32_t mode;
-  int32_t xcd;
   int32_t off32;        // the lattice read is under 4 GiB: 32-bit byte offsets
   Lev3 L;
   double *out;          // readout [n][4][512]: rho, ux, uy, uz
   double *part;         // readout [2 n][4]: mass, jx, jy, jz of the owned cells of each half block
   int32_t *err;
 };
-
-// Work item of workgroup bid: an entry of the launch's sequence [interior
-// blocks (n_fast) | other blocks | groups of 512 halo cells] (n entries), or
-// -1.  Workgroups go to the 8 XCDs round-robin; XCD x takes the x-th eighth
-// of the entries after the interior blocks (interface blocks and halo
-// groups: latency-bound, so they start first and are spread over all XCDs)
-// and then the x-th eighth of the interior blocks (contiguous in Morton
-// order, so neighbour reads stay in its own L2).  Without the remap the
-// entry is bid.
-__device__ __forceinline__ int remap3(int bid, int n, int n_fast, int enable) {
-  if (!enable) return bid < n ? bid : -1;
-  const int x = bid & 7, k = bid >> 3, ns = n - n_fast;
-  const int s0 = ns * x / 8, s1 = ns * (x + 1) / 8;
-  if (k < s1 - s0) return n_fast + s0 + k;
-  const int k2 = k - (s1 - s0);
-  const int r0 = n_fast * x / 8, r1 = n_fast * (x + 1) / 8;
-  return k2 < r1 - r0 ? r0 + k2 : -1;
-}
 
 __device__ __forceinline__ int nbr_slot(int sx, int sy, int sz) {
   const int ix = sx < 0 ? 0 : (sx >= kB3 ? 2 : 1);
@@ -454,34 +435,93 @@ __device__ __forceinline__ void band3(const Args3 &a, int packed) {
   for (int i = 0; i < Q; ++i) dst[((size_t)b * Q + i) * kC3 + cell] = g[i];
 }
 
-// MODE: 0 step (interior blocks first, then the rest, then halo cells),
-// M3_LOCAL, M3_READOUT or both.
-template <int ST, int Q, int MODE>
-__global__ __launch_bounds__(kWG3) void forest3_kernel(Args3 a) {
-  // work items: the two halves (z < 4, z >= 4) of each listed block, then
-  // groups of kWG3 halo cells
-  const int n_bg = (a.n_band + kWG3 - 1) / kWG3;
-  const int w2 = remap3(blockIdx.x, 2 * a.n_blocks + n_bg, 2 * a.n_fast, a.xcd);
-  if (w2 < 0) return;
-  if (w2 >= 2 * a.n_blocks) {
-    const int idx = (w2 - 2 * a.n_blocks) * kWG3 + threadIdx.x;
-    if (idx < a.n_band) band3<ST, Q>(a, a.band[idx]);
-    return;
+// Arguments of a step launch: the level substeps it runs, finest first, and
+// its work items: entry e covers n workgroups of one role of one substep.
+// The header and 7 entries fill the 16 words of one scalar load.
+enum : int32_t { R3_FAST = 0, R3_SLOW = 1, R3_BAND = 2 };
+struct Ent3 {
+  int32_t n, what;      // workgroups; substep << 2 | role
+};
+struct alignas(64) StepArgs3 {
+  int32_t n_ent, pad;
+  Ent3 ent[3 * kMaxLev3];
+  Args3 lv[kMaxLev3];
+};
+
+typedef __attribute__((address_space(4))) const StepArgs3 cstep3_t;
+typedef __attribute__((address_space(4))) const Args3 cargs3_t;
+typedef int int16_v3 __attribute__((ext_vector_type(16)));
+
+// Role, substep and index of workgroup bid (role -1: none).  Workgroups go
+// to the 8 XCDs round-robin; XCD x takes the x-th eighth of every entry
+// (interior blocks in Morton order, so neighbour reads stay in its own L2),
+// the latency-bound roles of all substeps first.
+__device__ __forceinline__ int step_role3(cstep3_t *s, int bid, int &seg, int &idx) {
+  const int16_v3 h = *(__attribute__((address_space(4))) const int16_v3 *)s;
+  const int x = bid & 7;
+  int k = bid >> 3;
+  auto takes = [&](int n, int what) -> bool {
+    const int lo = n * x >> 3, c = (n * (x + 1) >> 3) - lo;
+    idx = lo + k;
+    seg = what >> 2;
+    k -= c;
+    return k < 0;
+  };
+#pragma unroll
+  for (int e = 0; e < 7; ++e)
+    if (takes(h[2 + 2 * e], h[3 + 2 * e])) return h[3 + 2 * e] & 3;  // entries past the last are empty
+  const int n_ent = h[0];
+  for (int e = 7; e < n_ent; ++e) {
+    const int what = s->ent[e].what;
+    if (takes(s->ent[e].n, what)) return what & 3;
   }
-  const int w = w2 >> 1;
-  const int cell = (w2 & 1) * kWG3 + threadIdx.x;
-  const int b = __builtin_amdgcn_readfirstlane(a.list[w]);
-  if constexpr (MODE == 0) {
-    if (w < a.n_fast) {
-      if (a.off32) interior3<ST, Q, true>(a, b, cell);
-      else interior3<ST, Q, false>(a, b, cell);
-      return;
-    }
+  return -1;
+}
+
+// A pointer field of the launch arguments as a global pointer (read at a
+// substep index known only at run time it would lose its address space).
+template <class T>
+__device__ __forceinline__ T *global_field(__attribute__((address_space(4))) const void *f) {
+  const uint64_t v = *(__attribute__((address_space(4))) const uint64_t *)f;
+  return (T *)(__attribute__((address_space(1))) T *)v;
+}
+
+__device__ __forceinline__ Args3 load_step3(cargs3_t *p) {
+  Args3 a{};
+  a.meta = global_field<const Blk3>(&p->meta);
+  a.codes = global_field<const uint32_t>(&p->codes);
+  a.src = global_field<const char>(&p->src);
+  a.dst = global_field<char>(&p->dst);
+  a.fmeta = global_field<const Blk3>(&p->fmeta);
+  a.fprev = global_field<const char>(&p->fprev);
+  a.fcur = global_field<char>(&p->fcur);
+  a.band = global_field<const int32_t>(&p->band);
+  a.err = global_field<int32_t>(&p->err);
+  a.n_fast = p->n_fast;
+  a.n_band = p->n_band;
+  a.off32 = p->off32;
+  a.L.tau = p->L.tau;
+  a.L.pre = p->L.pre;
+  a.L.rho0 = p->L.rho0;
+  a.L.s_cf = p->L.s_cf;
+  a.L.s_fc = p->L.s_fc;
+  a.L.om_f = p->L.om_f;
+  a.L.pre_f = p->L.pre_f;
+  a.L.rho0_f = p->L.rho0_f;
+  a.L.s_cf_f = p->L.s_cf_f;
+  a.L.s_fc_f = p->L.s_fc_f;
+  a.L.rescale = p->L.rescale;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    a.L.F[q] = p->L.F[q];
+    a.L.F_f[q] = p->L.F_f[q];
   }
-  // the block's table and the neighbour tables of the 8 finer blocks under
-  // its octants (coalescence), in LDS
-  __shared__ Blk3 sk;
-  __shared__ int32_t cnb[8][27];
+  return a;
+}
+
+// The block's table and the neighbour tables of the 8 finer blocks under its
+// octants (coalescence), to LDS.
+__device__ __forceinline__ void stage_block3(const Args3 &a, int b, Blk3 &sk, int32_t (*cnb)[27]) {
   const int t = threadIdx.x;
   if (t < kBlkInts) reinterpret_cast<int32_t *>(&sk)[t] = reinterpret_cast<const int32_t *>(a.meta + b)[t];
   if (t < 8 * 27) {
@@ -490,10 +530,59 @@ __global__ __launch_bounds__(kWG3) void forest3_kernel(Args3 a) {
     cnb[o][sl] = cb >= 0 ? a.fmeta[cb].nbr[sl] : -1;
   }
   __syncthreads();
+}
+
+// The substeps of one launch: a substep of level l and the coarser levels'
+// substeps that follow it directly in Algorithm 1's order.  They do not
+// depend on each other: a coarser one coalesces from the lattice that the
+// finer one streams from, and explodes into halo blocks of the lattice that
+// the finer one writes owned blocks of.  Sharing a launch takes 2^V - 1 of
+// them a step to 2^(V-1), and lets the interface work of one level run
+// beside the interior of another.  Work items are half blocks (4 z-planes)
+// and groups of kWG3 halo cells.
+template <int ST, int Q>
+__global__ __launch_bounds__(kWG3) void forest3_step_kernel(StepArgs3) {
+  cstep3_t *args = (cstep3_t *)__builtin_amdgcn_kernarg_segment_ptr();
+  int seg0 = 0, w0 = 0;
+  const int role = __builtin_amdgcn_readfirstlane(step_role3(args, blockIdx.x, seg0, w0));
+  if (role < 0) return;
+  const int w2 = __builtin_amdgcn_readfirstlane(w0);
+  cargs3_t *lev = args->lv + __builtin_amdgcn_readfirstlane(seg0);
+  const Args3 a = load_step3(lev);
+  if (role == R3_BAND) {
+    const int idx = w2 * kWG3 + threadIdx.x;
+    if (idx < a.n_band) band3<ST, Q>(a, a.band[idx]);
+    return;
+  }
+  ci32_3 *list = (ci32_3 *)global_field<const int32_t>(&lev->list);
+  const int cell = (w2 & 1) * kWG3 + threadIdx.x;
+  if (role == R3_FAST) {
+    const int b = __builtin_amdgcn_readfirstlane(list[w2 >> 1]);
+    if (a.off32) interior3<ST, Q, true>(a, b, cell);
+    else interior3<ST, Q, false>(a, b, cell);
+    return;
+  }
+  const int b = __builtin_amdgcn_readfirstlane(list[a.n_fast + (w2 >> 1)]);
+  __shared__ Blk3 sk;
+  __shared__ int32_t cnb[8][27];
+  stage_block3(a, b, sk, cnb);
+  double part[4];
+  cell3<ST, Q>(a, sk, cnb, b, 0, cell, part);
+}
+
+// The initial collision and the readouts, over listed blocks.  MODE:
+// M3_LOCAL, M3_READOUT or both.
+template <int ST, int Q, int MODE>
+__global__ __launch_bounds__(kWG3) void forest3_kernel(Args3 a) {
+  const int w2 = blockIdx.x, w = w2 >> 1, t = threadIdx.x;
+  const int b = __builtin_amdgcn_readfirstlane(a.list[w]);
+  __shared__ Blk3 sk;
+  __shared__ int32_t cnb[8][27];
+  stage_block3(a, b, sk, cnb);
   double part[4] = {0.0, 0.0, 0.0, 0.0};
   Args3 m = a;
   m.mode = MODE;
-  cell3<ST, Q>(m, sk, cnb, b, w, cell, part);
+  cell3<ST, Q>(m, sk, cnb, b, w, (w2 & 1) * kWG3 + t, part);
   if constexpr ((MODE & M3_READOUT) != 0) {  // fixed-order tree over the half block's cells
     __shared__ double red[4][kWG3];
 #pragma unroll
@@ -543,29 +632,42 @@ __global__ __launch_bounds__(kC3) void init3f_kernel(const int32_t *list, const 
   }
 }
 
-// Workgroups of a launch over n list entries: with the XCD remap, 8 times
-// the largest share of one XCD.
-int grid3(int n, int n_fast, int remap) {
-  if (!remap) return n;
-  int most = 0;
-  for (int x = 0; x < 8; ++x) {
-    const int ns = n - n_fast;
-    most = std::max(most, (ns * (x + 1) / 8 - ns * x / 8) + (n_fast * (x + 1) / 8 - n_fast * x / 8));
-  }
-  return 8 * most;
-}
-
 template <int ST, int Q>
 hipError_t launch_forest3(const Args3 &a, hipStream_t s) {
-  const int n = grid3(2 * a.n_blocks + (a.n_band + kWG3 - 1) / kWG3, 2 * a.n_fast, a.xcd);
+  const int n = 2 * a.n_blocks;
   if (n <= 0) return hipSuccess;
   switch (a.mode) {
-    case 0: hipLaunchKernelGGL((forest3_kernel<ST, Q, 0>), dim3(n), dim3(kWG3), 0, s, a); break;
     case M3_LOCAL: hipLaunchKernelGGL((forest3_kernel<ST, Q, M3_LOCAL>), dim3(n), dim3(kWG3), 0, s, a); break;
     case M3_READOUT: hipLaunchKernelGGL((forest3_kernel<ST, Q, M3_READOUT>), dim3(n), dim3(kWG3), 0, s, a); break;
-    default:
+    case M3_LOCAL | M3_READOUT:
       hipLaunchKernelGGL((forest3_kernel<ST, Q, M3_LOCAL | M3_READOUT>), dim3(n), dim3(kWG3), 0, s, a);
+      break;
+    default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+// One launch of the substeps lv[0 .. n), finest first.
+template <int ST, int Q>
+hipError_t launch_step3f(const Args3 *lv, int n, hipStream_t s) {
+  StepArgs3 t;
+  memset(&t, 0, sizeof(t));
+  const int order[3] = {R3_SLOW, R3_BAND, R3_FAST};
+  for (int i = 0; i < n; ++i) t.lv[i] = lv[i];
+  for (int r : order)
+    for (int i = 0; i < n; ++i) {
+      const int c = r == R3_FAST ? 2 * lv[i].n_fast
+                                 : (r == R3_SLOW ? 2 * (lv[i].n_blocks - lv[i].n_fast) : (lv[i].n_band + kWG3 - 1) / kWG3);
+      if (c > 0) t.ent[t.n_ent++] = {c, i << 2 | r};
+    }
+  int most = 0;
+  for (int x = 0; x < 8; ++x) {
+    int c = 0;
+    for (int e = 0; e < t.n_ent; ++e) c += (t.ent[e].n * (x + 1) >> 3) - (t.ent[e].n * x >> 3);
+    most = std::max(most, c);
+  }
+  if (most == 0) return hipSuccess;
+  hipLaunchKernelGGL((forest3_step_kernel<ST, Q>), dim3(8 * most), dim3(kWG3), 0, s, t);
   return hipGetLastError();
 }
 
@@ -577,21 +679,24 @@ hipError_t launch_init3f(const int32_t *list, int n, const Blk3 *meta, const uin
   return hipGetLastError();
 }
 
+#define FOREST3_DISPATCH(F, ...)           \
+  switch (st + 4 * (q == 27)) {            \
+    case 0: return F<0, 19>(__VA_ARGS__);  \
+    case 1: return F<1, 19>(__VA_ARGS__);  \
+    case 2: return F<2, 19>(__VA_ARGS__);  \
+    case 3: return F<3, 19>(__VA_ARGS__);  \
+    case 4: return F<0, 27>(__VA_ARGS__);  \
+    case 5: return F<1, 27>(__VA_ARGS__);  \
+    case 6: return F<2, 27>(__VA_ARGS__);  \
+    default: return F<3, 27>(__VA_ARGS__); \
+  }
+
 hipError_t forest3_dispatch(int st, int q, const Args3 &a, hipStream_t s) {
-  if (q == 19) {
-    switch (st) {
-      case 0: return launch_forest3<0, 19>(a, s);
-      case 1: return launch_forest3<1, 19>(a, s);
-      case 2: return launch_forest3<2, 19>(a, s);
-      default: return launch_forest3<3, 19>(a, s);
-    }
-  }
-  switch (st) {
-    case 0: return launch_forest3<0, 27>(a, s);
-    case 1: return launch_forest3<1, 27>(a, s);
-    case 2: return launch_forest3<2, 27>(a, s);
-    default: return launch_forest3<3, 27>(a, s);
-  }
+  FOREST3_DISPATCH(launch_forest3, a, s)
+}
+
+hipError_t step3f_dispatch(int st, int q, const Args3 *lv, int n, hipStream_t s) {
+  FOREST3_DISPATCH(launch_step3f, lv, n, s)
 }
 
 hipError_t init3f_dispatch(int st, int q, const int32_t *list, int n, const Blk3 *meta, const uint32_t *codes,
@@ -1063,10 +1168,9 @@ void rec3(int l, int V, std::vector<std::pair<int, int>> &out) {
   out.push_back({l, 2});
 }
 
-// One launch of level l over n blocks of `list` (pool indices) and, in a
-// step launch, n_band halo cells.
-sbt_status launch_level3(sbt3f_ctx &X, int l, const int32_t *list, int n, int mode, bool flip, int n_band = 0) {
-  Pool3 &P = X.pools[l];
+// Arguments of a launch of level l in the current state.
+Args3 args3(const sbt3f_ctx &X, int l, int mode) {
+  const Pool3 &P = X.pools[l];
   Args3 a{};
   a.meta = P.d_meta;
   a.codes = P.d_codes;
@@ -1076,33 +1180,48 @@ sbt_status launch_level3(sbt3f_ctx &X, int l, const int32_t *list, int n, int mo
   // read: its streamed state is the oracle's pre-collision state
   if ((mode & M3_READOUT) && !(mode & M3_LOCAL)) a.src = P.lat[1 - P.cur];
   if (l + 1 < X.fo.m) {
-    Pool3 &F = X.pools[l + 1];
+    const Pool3 &F = X.pools[l + 1];
     a.fmeta = F.d_meta;
     a.fprev = F.lat[1 - F.cur];
     a.fcur = F.lat[F.cur];
   }
-  a.list = list;
-  a.n_blocks = n;
-  a.n_fast = mode == 0 ? P.n_fast : 0;
-  a.band = P.d_band;
-  a.n_band = mode == 0 ? n_band : 0;
   a.mode = mode;
-  a.xcd = mode == 0 ? 1 : 0;
   a.off32 = ((size_t)P.n_own + P.n_halo) * X.q * kC3 * stor_bytes3(X.storage) < ((size_t)1 << 32);
   a.L = P.L;
   a.out = X.d_stage;
   a.part = X.d_part;
   a.err = X.d_err;
+  return a;
+}
+
+// One launch of level l over n blocks of `list` (pool indices): the initial
+// collision or a readout.
+sbt_status launch_level3(sbt3f_ctx &X, int l, const int32_t *list, int n, int mode, bool flip) {
+  Args3 a = args3(X, l, mode);
+  a.list = list;
+  a.n_blocks = n;
   HIPCHK3(forest3_dispatch(X.storage, X.q, a, X.stream));
-  if (flip) P.cur ^= 1;
+  if (flip) X.pools[l].cur ^= 1;
   return SBT_OK;
 }
 
-// Substep p (1 or 2) of level l: the blocks with owned cells, and in the
-// first of a fine level's two substeps its halo cells.
-sbt_status substep3(sbt3f_ctx &X, int l, int p) {
-  Pool3 &P = X.pools[l];
-  return launch_level3(X, l, P.d_list, P.n_own, 0, true, (p == 1 && l > 0) ? P.n_band : 0);
+// The substeps ph[0 .. n) as one launch (finest first, each one level coarser
+// than the one before; see forest3_step_kernel): the blocks with owned cells
+// and, in the first of a fine level's two substeps, its halo cells.
+sbt_status launch_substeps3(sbt3f_ctx &X, const std::pair<int, int> *ph, int n) {
+  Args3 lv[kMaxLev3];
+  for (int i = 0; i < n; ++i) {
+    Pool3 &P = X.pools[ph[i].first];
+    Args3 &a = lv[i] = args3(X, ph[i].first, 0);
+    a.list = P.d_list;
+    a.n_blocks = P.n_own;
+    a.n_fast = P.n_fast;
+    a.band = P.d_band;
+    a.n_band = ph[i].second == 1 && ph[i].first > 0 ? P.n_band : 0;
+    P.cur ^= 1;
+  }
+  HIPCHK3(step3f_dispatch(X.storage, X.q, lv, n, X.stream));
+  return SBT_OK;
 }
 
 // The first collision of every level from the initial pre-collision state,
@@ -1325,9 +1444,12 @@ sbt_status sbt3f_step(sbt3f_ctx *ctx, int32_t n) {
     if (st) return st;
   }
   for (int t = 0; t < n; ++t)
-    for (const auto &ph : X.phases) {
-      sbt_status st = substep3(X, ph.first, ph.second);
+    for (size_t i = 0; i < X.phases.size();) {
+      size_t n = 1;
+      while (i + n < X.phases.size() && X.phases[i + n].first == X.phases[i + n - 1].first - 1) ++n;
+      sbt_status st = launch_substeps3(X, &X.phases[i], (int)n);
       if (st) return st;
+      i += n;
     }
   return SBT_OK;
 }
