@@ -21,7 +21,7 @@ def build(verbose=False, jobs=2):
     objs = []
     procs = []
     for src in ("sbt_kernels.hip", "sbt_persist.hip", "sbt_stats.hip", "sbt3d.hip", "sbt3f.hip", "sbt_static.hip",
-                "sbt_host.cpp"):
+                "sbt_host.cpp", "host_copy.cpp"):
         obj = os.path.join(csrc, src.rsplit(".", 1)[0] + ".o")
         lang = ["-x", "hip"] if src.endswith(".hip") else []
         cmd = ["hipcc", *HIP_FLAGS, *inc, *lang, "-c", os.path.join(csrc, src), "-o", obj]
@@ -37,7 +37,7 @@ def build(verbose=False, jobs=2):
     if any(rc):
         raise RuntimeError(f"hipcc failed: {rc}")
     tmp = LIB + ".tmp"
-    cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
+    cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-lpthread", "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

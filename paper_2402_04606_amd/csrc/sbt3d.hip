@@ -14,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "host_copy.h"
 #include "lattice3.h"
 #include "sbt3d.h"
 #include "sbt_internal.h"
@@ -739,6 +740,7 @@ struct sbt3_ctx {
   long long n_records = 0;
   Ibm3 ibm{};                 // immersed body (ibm.n == 0: none)
   long long ibm_t = 0;        // step of the next forcing loop
+  sbt::HostCopy copy;
 };
 
 namespace {
@@ -1222,9 +1224,9 @@ sbt_status sbt3_read_slab(sbt3_ctx *ctx, int32_t z0, int32_t nz, double *rho, do
     HIP3(SBT3_LAUNCH(read3_kernel, X.d.storage, X.d.lattice, dim3((unsigned)((m + kThreads - 1) / kThreads)), X.stream, X.p, src,
                      X.stage, (long long)z0 * plane + k0, m, X.post ? 1 : 0));
     double *dst[4] = {rho, ux, uy, uz};
-    for (int q = 0; q < 4; ++q)
-      HIP3(hipMemcpyAsync(dst[q] + k0, X.stage + q * m, sizeof(double) * m, hipMemcpyDeviceToHost, X.stream));
-    HIP3(hipStreamSynchronize(X.stream));
+    sbt::HostCopy::Piece pc[4];
+    for (int q = 0; q < 4; ++q) pc[q] = {X.stage + q * m, dst[q] + k0, sizeof(double) * (size_t)m};
+    HIP3(X.copy.to_host(pc, 4, X.stream));
   }
   return SBT_OK;
 }

@@ -29,6 +29,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "host_copy.h"
 #include "lattice3.h"
 #include "sbt3f.h"
 #include "sbt_internal.h"
@@ -84,7 +85,8 @@ struct Args3 {
   int32_t mode;
   int32_t off32;        // the lattice read is under 4 GiB: 32-bit byte offsets
   Lev3 L;
-  double *out;          // readout [n][4][512]: rho, ux, uy, uz
+  double *out;          // readout of a box, [4][z][y][x]: rho, ux, uy, uz (null: none)
+  int32_t box[6];       // that box: origin and size, cells of the level
   double *part;         // readout [2 n][4]: mass, jx, jy, jz of the owned cells of each half block
   int32_t *err;
 };
@@ -153,7 +155,7 @@ __device__ __forceinline__ Calc3<ST> feq3(const Lev3 &L, int i, Calc3<ST> rho, C
 // One cell of a level launch; part gets its mass and first moment in a
 // readout.
 template <int ST, int Q>
-__device__ __forceinline__ void cell3(const Args3 &a, const Blk3 &k, const int32_t (*cnb)[27], int b, int w, int cell,
+__device__ __forceinline__ void cell3(const Args3 &a, const Blk3 &k, const int32_t (*cnb)[27], int b, int cell,
                                       double part[4]) {
 #pragma clang fp contract(off)
   using S = Store3<ST>;
@@ -165,13 +167,7 @@ __device__ __forceinline__ void cell3(const Args3 &a, const Blk3 &k, const int32
   T *dst = static_cast<T *>(a.dst);
 
   if (k.flags & B3_GHOST) return;  // halo blocks: their cells go through band3
-  if (code & K3_HIDDEN) {
-    if (a.mode & M3_READOUT) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) a.out[((size_t)w * 4 + q) * kC3 + cell] = __builtin_nan("");
-    }
-    return;
-  }
+  if (code & K3_HIDDEN) return;
 
   C f[Q];
   if (a.mode & M3_LOCAL) {
@@ -227,10 +223,14 @@ __device__ __forceinline__ void cell3(const Args3 &a, const Blk3 &k, const int32
       jz += E3Z[i] * v;
     }
     if constexpr (ST != 0) rho = a.L.rho0 + rho;
-    a.out[((size_t)w * 4 + 0) * kC3 + cell] = rho;
-    a.out[((size_t)w * 4 + 1) * kC3 + cell] = (jx + 0.5 * a.L.F[0]) / rho;
-    a.out[((size_t)w * 4 + 2) * kC3 + cell] = (jy + 0.5 * a.L.F[1]) / rho;
-    a.out[((size_t)w * 4 + 3) * kC3 + cell] = (jz + 0.5 * a.L.F[2]) / rho;
+    const int px = k.ox + x - a.box[0], py = k.oy + y - a.box[1], pz = k.oz + z - a.box[2];
+    if (a.out && (unsigned)px < (unsigned)a.box[3] && (unsigned)py < (unsigned)a.box[4] && (unsigned)pz < (unsigned)a.box[5]) {
+      const size_t n = (size_t)a.box[3] * a.box[4] * a.box[5], i = ((size_t)pz * a.box[4] + py) * a.box[3] + px;
+      a.out[i] = rho;
+      a.out[n + i] = (jx + 0.5 * a.L.F[0]) / rho;
+      a.out[2 * n + i] = (jy + 0.5 * a.L.F[1]) / rho;
+      a.out[3 * n + i] = (jz + 0.5 * a.L.F[2]) / rho;
+    }
     part[0] = rho;
     part[1] = jx;
     part[2] = jy;
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kWG3) void forest3_step_kernel(StepArgs3) {
   __shared__ int32_t cnb[8][27];
   stage_block3(a, b, sk, cnb);
   double part[4];
-  cell3<ST, Q>(a, sk, cnb, b, 0, cell, part);
+  cell3<ST, Q>(a, sk, cnb, b, cell, part);
 }
 
 // The initial collision and the readouts, over listed blocks.  MODE:
@@ -582,7 +582,7 @@ __global__ __launch_bounds__(kWG3) void forest3_kernel(Args3 a) {
   double part[4] = {0.0, 0.0, 0.0, 0.0};
   Args3 m = a;
   m.mode = MODE;
-  cell3<ST, Q>(m, sk, cnb, b, w, (w2 & 1) * kWG3 + t, part);
+  cell3<ST, Q>(m, sk, cnb, b, (w2 & 1) * kWG3 + t, part);
   if constexpr ((MODE & M3_READOUT) != 0) {  // fixed-order tree over the half block's cells
     __shared__ double red[4][kWG3];
 #pragma unroll
@@ -1079,6 +1079,7 @@ struct sbt3f_ctx {
   int32_t *d_err = nullptr;
   bool post = false;   // false: the lattices hold the initial pre-collision state
   std::vector<std::pair<int, int>> phases;  // (level, substep parity 1 or 2) of one coarse step
+  sbt::HostCopy copy;
 };
 
 namespace {
@@ -1188,7 +1189,6 @@ Args3 args3(const sbt3f_ctx &X, int l, int mode) {
   a.mode = mode;
   a.off32 = ((size_t)P.n_own + P.n_halo) * X.q * kC3 * stor_bytes3(X.storage) < ((size_t)1 << 32);
   a.L = P.L;
-  a.out = X.d_stage;
   a.part = X.d_part;
   a.err = X.d_err;
   return a;
@@ -1196,8 +1196,13 @@ Args3 args3(const sbt3f_ctx &X, int l, int mode) {
 
 // One launch of level l over n blocks of `list` (pool indices): the initial
 // collision or a readout.
-sbt_status launch_level3(sbt3f_ctx &X, int l, const int32_t *list, int n, int mode, bool flip) {
+sbt_status launch_level3(sbt3f_ctx &X, int l, const int32_t *list, int n, int mode, bool flip,
+                         const int32_t *box = nullptr) {
   Args3 a = args3(X, l, mode);
+  if (box) {  // a readout of that box into the staging area
+    a.out = X.d_stage;
+    for (int i = 0; i < 6; ++i) a.box[i] = box[i];
+  }
   a.list = list;
   a.n_blocks = n;
   HIPCHK3(forest3_dispatch(X.storage, X.q, a, X.stream));
@@ -1470,34 +1475,37 @@ sbt_status sbt3f_read_box(sbt3f_ctx *ctx, int32_t level, const int32_t box[6], d
   if (st) return st;
   if (!rho || !ux || !uy || !uz) return fail3(SBT_ERR_ARG, "null field array");
   sbt3f_ctx &X = *ctx;
-  const size_t nc = (size_t)box[3] * box[4] * box[5];
-  for (size_t i = 0; i < nc; ++i) rho[i] = ux[i] = uy[i] = uz[i] = __builtin_nan("");
-  const LevelHost &H = X.fo.L[level];
-  const std::vector<int32_t> blocks = blocks_in_box(X, level, box);
+  // Part boxes that the staging area holds and that lie in one piece in the
+  // caller's arrays: whole planes, else rows of one plane, else cells of one
+  // row.  The device lays each out densely, NaN where the level owns no cell.
+  const int64_t cap = (int64_t)stage_blocks(X) * kC3, row = box[3], plane = row * box[4];
+  const int nz = (int)std::max<int64_t>(1, cap / plane);
+  const int ny = plane <= cap ? box[4] : (int)std::max<int64_t>(1, cap / row);
+  const int nx = row <= cap ? box[3] : (int)cap;
   const int sb = stage_blocks(X);
-  std::vector<double> stage((size_t)sb * 4 * kC3);
-  for (size_t b0 = 0; b0 < blocks.size(); b0 += sb) {
-    const int nb = (int)std::min<size_t>(sb, blocks.size() - b0);
-    HIPCHK3(hipMemcpyAsync(X.d_stage_list, blocks.data() + b0, (size_t)nb * 4, hipMemcpyHostToDevice, X.stream));
-    st = launch_level3(X, level, X.d_stage_list, nb, M3_READOUT | (X.post ? 0 : M3_LOCAL), false);
-    if (st) return st;
-    HIPCHK3(hipMemcpyAsync(stage.data(), X.d_stage, (size_t)nb * 4 * kC3 * 8, hipMemcpyDeviceToHost, X.stream));
-    HIPCHK3(hipStreamSynchronize(X.stream));
-    for (int w = 0; w < nb; ++w) {
-      int bx, by, bz;
-      H.unkey(H.own_keys[blocks[b0 + w]], bx, by, bz);
-      for (int c = 0; c < kC3; ++c) {
-        const int x = bx * 8 + (c & 7) - box[0], y = by * 8 + ((c >> 3) & 7) - box[1], z = bz * 8 + (c >> 6) - box[2];
-        if (x < 0 || y < 0 || z < 0 || x >= box[3] || y >= box[4] || z >= box[5]) continue;
-        const size_t i = ((size_t)z * box[4] + y) * box[3] + x;
-        const double *s = stage.data() + (size_t)w * 4 * kC3 + c;
-        rho[i] = s[0];
-        ux[i] = s[kC3];
-        uy[i] = s[2 * kC3];
-        uz[i] = s[3 * kC3];
+  for (int z = 0; z < box[5]; z += nz)
+    for (int y = 0; y < box[4]; y += ny)
+      for (int x = 0; x < box[3]; x += nx) {
+        const int32_t part[6] = {box[0] + x, box[1] + y, box[2] + z, std::min(nx, box[3] - x), std::min(ny, box[4] - y),
+                                 std::min(nz, box[5] - z)};
+        const size_t n = (size_t)part[3] * part[4] * part[5], at = (size_t)z * plane + (size_t)y * row + x;
+        const std::vector<int32_t> blocks = blocks_in_box(X, level, part);
+        if (blocks.empty()) {
+          for (double *f : {rho, ux, uy, uz}) std::fill(f + at, f + at + n, __builtin_nan(""));
+          continue;
+        }
+        HIPCHK3(sbt_launch_fill_nan(X.d_stage, 4 * n, SBT_F64, X.stream));
+        for (size_t b0 = 0; b0 < blocks.size(); b0 += sb) {
+          const int nb = (int)std::min<size_t>(sb, blocks.size() - b0);
+          HIPCHK3(hipMemcpyAsync(X.d_stage_list, blocks.data() + b0, (size_t)nb * 4, hipMemcpyHostToDevice, X.stream));
+          st = launch_level3(X, level, X.d_stage_list, nb, M3_READOUT | (X.post ? 0 : M3_LOCAL), false, part);
+          if (st) return st;
+        }
+        double *dst[4] = {rho, ux, uy, uz};
+        sbt::HostCopy::Piece pc[4];
+        for (int q = 0; q < 4; ++q) pc[q] = {X.d_stage + q * n, dst[q] + at, n * sizeof(double)};
+        HIPCHK3(X.copy.to_host(pc, 4, X.stream));
       }
-    }
-  }
   return SBT_OK;
 }
 
