@@ -216,6 +216,9 @@ hipError_t sbt_launch_level(int storage, int tile, const sbt::LevelArgs *a, hipS
 // finer level or a domain edge; then n_solid blocks with solid cells and
 // n_band packed halo-band cells.
 hipError_t sbt_launch_level_tile(int storage, const sbt::LevelArgs *a, int n, hipStream_t s);
+// ns (2 or 4) steps of the interior blocks a->list[0 .. n_fast) of a periodic
+// level in one launch; the lattice read must be under 4 GiB.
+hipError_t sbt_launch_multi_step(int storage, int ns, const sbt::LevelArgs *a, hipStream_t s);
 // One step as a single persistent launch of `groups` 1024-lane workgroups
 // (all resident at once) over the phase table `ph` (n_ph entries, device
 // memory), phases separated by grid barriers on bar[3] (zero between

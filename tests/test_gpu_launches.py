@@ -155,3 +155,32 @@ def test_forcing_loop3_matches_oracle(env, n, moving):
         assert np.array_equal(g.body_force(), o.body_force())
     for a, b in zip(g.fields(), o.fields()):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s", "bf16s"])
+@pytest.mark.parametrize("sizes,mrt", [(((16, 16),), False), (((48, 32), (16, 80)), True), (((272, 256),), False),
+                                       (((512, 528),), True)])
+def test_steps_that_share_a_launch(env, storage, sizes, mrt):
+    """Calls of many steps against single steps, bit for bit, state included:
+    a block that is its own neighbour, a batch, 256 blocks and more (four or
+    two steps a launch), a body force, every remainder of a call."""
+    P, O = env
+    wls = []
+    for c, (nx, ny) in enumerate(sizes):
+        wl = W.tgv(64, tau=0.6 + 0.1 * c, u0=0.03)
+        wls.append(wl.replace(nx0=nx, ny0=ny, fext=(1e-5, -2e-5), collision=W.COLL_MRT if mrt else W.COLL_BGK))
+    print(sizes, storage, mrt, flush=True)
+    one, many = P.Sim(wls, storage), P.Sim(wls, storage)
+    for n in (5, 6, 7, 8, 9, 13, 1, 26):
+        for _ in range(n):
+            one.step(1)
+        many.step(n)
+        many.synchronize()
+        assert np.array_equal(one.read_state(), many.read_state()), n
+    for c in range(len(wls)):
+        for a, b in zip(one.fields(c, 0), many.fields(c, 0)):
+            assert np.array_equal(a, b)
+    if storage == "f64" and not mrt and sizes[0][0] < 100:
+        o = O.OracleSim(wls[0])
+        o.step(75)
+        equal_levels(many, o, wls[0])
