@@ -344,7 +344,9 @@ sbt_status sbt_autotune(sbt_ctx *ctx, int32_t steps, const char *cache_path);
  * out[4] = algorithmic bytes moved by the level kernels (2 Q s per cell
  * update), out[5] = cell updates, out[6] = ms of the tile kernel (all owned
  * blocks and halo bands; substeps that do not depend on each other share a
- * launch), out[7] = its launch count, out[8] = its algorithmic bytes. */
+ * launch), out[7] = its launch count, out[8] = its algorithmic bytes.
+ * Forcing loops, which otherwise may share a launch with the level substeps
+ * that follow them, run in launches of their own here. */
 sbt_status sbt_profile(sbt_ctx *ctx, int32_t n, double out[9]);
 /* Cell updates performed per sbt_step, summed over cases and levels. */
 sbt_status sbt_updates_per_step(sbt_ctx *ctx, int64_t *updates);

@@ -268,7 +268,7 @@ struct Phase {
 
 }  // namespace
 
-// Polls of a persistent-step grid-barrier wait before it gives up (with a
+// Polls of a wait inside a launch before it gives up (with a
 // short sleep each, about a second).
 constexpr uint32_t kBarrierSpins = 1u << 21;
 
@@ -311,7 +311,7 @@ struct sbt_ctx {
   bool plans_ready = false;     // the plans the next step takes as given are built
 
   std::vector<Phase> step_phases;
-  std::vector<hipGraphExec_t> graph;   // [level-0 parity + 2 * plan buffer + 2 * plan_bufs * size index]
+  std::vector<hipGraphExec_t> graph;   // [graph_slot]
   hipEvent_t step_event = nullptr;
   bool graph_dirty = true;
   size_t bytes_used = 0;
@@ -814,11 +814,10 @@ sbt_status timed_launch(sbt_ctx &X, bool fast, hipStream_t s, F &&launch) {
   return SBT_OK;
 }
 
-// The level substeps ph[0 .. n) (finest first, each one level coarser than
-// the one before) as one launch; see level_tile_kernel for why they do not
-// depend on each other.
-sbt_status launch_substeps(sbt_ctx &X, const Phase *ph, int n, hipStream_t s) {
-  LevelArgs lv[kMaxLevels];
+// Arguments of the level substeps ph[0 .. n) (finest first, each one level
+// coarser than the one before), which advance the host's state; returns
+// whether they have any work.  `sums`: the launch forms F_s too.
+bool substep_args(sbt_ctx &X, const Phase *ph, int n, bool sums, LevelArgs *lv) {
   bool any = false;
   for (int i = 0; i < n; ++i) {
     Pool &P = X.pools[ph[i].v];
@@ -833,14 +832,22 @@ sbt_status launch_substeps(sbt_ctx &X, const Phase *ph, int n, hipStream_t s) {
       t.band = P.d_band;
       t.n_band = (int)P.band.size();
     }
-    if (ph[i].v == X.V - 1 && X.n_bodies > 0) {  // follows the forcing loops of the substep
+    if (sums && ph[i].v == X.V - 1 && X.n_bodies > 0) {  // follows the forcing loops of the substep
       t.bodies = X.d_bodies;
       t.n_sum = X.n_bodies;
     }
     any |= t.n_blocks + t.n_solid + t.n_band + t.n_sum > 0;
     P.cur = 1 - P.cur;
   }
-  return any ? timed_launch(X, true, s, [&] { return sbt_launch_level_tile(X.kvar, lv, n, s); }) : SBT_OK;
+  return any;
+}
+
+// Those substeps as one launch; see level_tile_kernel for why they do not
+// depend on each other.
+sbt_status launch_substeps(sbt_ctx &X, const Phase *ph, int n, hipStream_t s) {
+  LevelArgs lv[kMaxLevels];
+  if (!substep_args(X, ph, n, true, lv)) return SBT_OK;
+  return timed_launch(X, true, s, [&] { return sbt_launch_level_tile(X.kvar, lv, n, s); });
 }
 
 // Every owned block of pool v through the generic kernel (the first
@@ -875,16 +882,58 @@ MdfArgs mdf_args(const sbt_ctx &X, bool first) {
 
 IbmArgs prep_args(const sbt_ctx &X, int n_plans, int n_moving, bool fixed);
 
-sbt_status launch_mdf(sbt_ctx &X, bool first, hipStream_t s) {
-  if (X.n_bodies == 0) return SBT_OK;
-  MdfArgs a = mdf_args(X, first);
+// The plans that the forcing-loop launch of the next substep builds beside it.
+IbmArgs beside_args(const sbt_ctx &X) {
   IbmArgs p = prep_args(X, 0, X.plan_chunk, false);
   if (X.plan_chunk > 0 && X.k_host % X.plan_chunk == 0) {
     p.n_plans = X.plan_chunk;
     p.first = X.plan_bufs - X.plan_chunk;
-    p.beside = a.parity;
+    p.beside = (int)(X.k_host & (X.plan_bufs - 1));
     p.lds_window = X.lds_window_beside;
   }
+  return p;
+}
+
+// Whether the forcing loops and the level substeps ph[0 .. n) that follow
+// them share a launch (mdf_level_kernel).  The collisions then run beside the
+// loops and one launch is saved, but at half the wavefronts of a level launch
+// (the loop's registers and LDS), which costs more than it saves where the
+// blocks are many, sooner with 2-byte storage, which has fewer bytes in
+// flight per wavefront.  Measured, us a step apart / shared: a cylinder of
+// 126 markers on 512 blocks F64 19.7 / 17.1, F32 17.7 / 13.8, F16S 17.5 /
+// 13.9; on 2048 28.0 / 24.7, 20.9 / 16.4, 18.3 / 15.0; on 4608 42.1 / 40.1,
+// 28.0 / 21.8, 22.8 / 21.4; on 8192 68.5 / 71.3, 36.9 / 33.8, 28.0 / 32.8; on
+// 18432 144 / 151, 77.5 / 84.5, 40.6 / 63.0.  32 wings, the launches of up to
+// 4096 items shared: 943 / 898, 496 / 473, 347 / 338; up to 8192 of 64 wings:
+// 1675 / 1624, 862 / 839, 565 / 570.
+bool forcing_shares(const sbt_ctx &X, const Phase *ph, int n) {
+  if (X.n_bodies == 0 || X.profiling || X.max_body_markers > kMaxMarkers / 2) return false;
+  int64_t items = 0;
+  for (int i = 0; i < n; ++i) {
+    const Pool &P = X.pools[ph[i].v];
+    const int kpw = ph[i].v < (int)X.kpw_level.size() ? X.kpw_level[ph[i].v] : 0;
+    if (!P.solid.empty() || kpw > 1) return false;
+    items += (int64_t)(P.fast.size() + P.slow.size()) + (ph[i].p == 1 ? ((int64_t)P.band.size() + 255) / 256 : 0);
+  }
+  return items <= (X.storage == SBT_F64 ? 6656 : (X.storage == SBT_F32 ? 8192 : 4096));
+}
+
+// One launch of the forcing loops and the level substeps ph[0 .. n).
+sbt_status launch_forcing_shared(sbt_ctx &X, const Phase *ph, int n, hipStream_t s) {
+  const MdfArgs a = mdf_args(X, false);
+  const IbmArgs p = beside_args(X);
+  ++X.k_host;
+  LevelArgs lv[kMaxLevels];
+  substep_args(X, ph, n, false, lv);
+  for (int i = 0; i < n; ++i) lv[i].kpw = 1;
+  HIPCHK(sbt_launch_mdf_level(X.kvar, &a, &p, X.n_bodies, (int)(X.k_host & 1), kBarrierSpins, lv, n, s));
+  return SBT_OK;
+}
+
+sbt_status launch_mdf(sbt_ctx &X, bool first, hipStream_t s) {
+  if (X.n_bodies == 0) return SBT_OK;
+  const MdfArgs a = mdf_args(X, first);
+  const IbmArgs p = beside_args(X);
   ++X.k_host;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (X.profiling) {
@@ -981,15 +1030,18 @@ sbt_status run_step_eager(sbt_ctx &X, hipStream_t s) {
   if (st) return st;
   const std::vector<Phase> &ph = X.step_phases;
   for (size_t i = 0; i < ph.size() && !st;) {
-    if (ph[i].type == PH_MDF) {
-      st = launch_mdf(X, false, s);
-      ++i;
-      continue;
-    }
-    // a substep and the coarser levels' substeps that follow it directly
+    // the forcing loops (where there are any), a substep and the coarser
+    // levels' substeps that follow it directly
+    const bool forced = ph[i].type == PH_MDF;
+    i += forced;
     size_t n = 1;
     while (i + n < ph.size() && ph[i + n].type == PH_LEVEL && ph[i + n].v == ph[i + n - 1].v - 1) ++n;
-    st = launch_substeps(X, &ph[i], (int)n, s);
+    if (forced && forcing_shares(X, &ph[i], (int)n)) {
+      st = launch_forcing_shared(X, &ph[i], (int)n, s);
+    } else {
+      if (forced) st = launch_mdf(X, false, s);
+      if (!st) st = launch_substeps(X, &ph[i], (int)n, s);
+    }
     i += n;
   }
   return st;
@@ -1092,9 +1144,13 @@ sbt_status run_step_persistent(sbt_ctx &X, hipStream_t s) {
 // steps, so the launch gap between graphs is paid once per 4 steps.
 constexpr int kGraphSteps[3] = {1, 2, 4};
 
+// Forcing-loop counters that a graph tells apart: those of the plan buffers,
+// and odd from even ones, for which a shared launch waits.
+int graph_ks(const sbt_ctx &X) { return std::max(X.plan_bufs, 2); }
+
 sbt_status ensure_capture_stream(sbt_ctx &X) {
   if (!X.cap_stream) HIPCHK(hipStreamCreateWithFlags(&X.cap_stream, hipStreamNonBlocking));
-  if ((int)X.graph.size() != 3 * 2 * X.plan_bufs) X.graph.assign(3 * 2 * X.plan_bufs, nullptr);
+  if ((int)X.graph.size() != 3 * 2 * graph_ks(X)) X.graph.assign(3 * 2 * graph_ks(X), nullptr);
   return SBT_OK;
 }
 
@@ -1102,9 +1158,9 @@ sbt_status ensure_capture_stream(sbt_ctx &X) {
 // substeps.  Over a step only level 0's parity flips (every finer level
 // runs an even number of substeps) and the forcing-loop counter advances by
 // the number of plan buffers, so the key is level 0's parity and the plan
-// buffer of the step's first substep.
+// buffer (and parity) of the step's first substep.
 int graph_slot(const sbt_ctx &X, int si) {
-  return X.pools[0].cur + 2 * (int)(X.k_host & (X.plan_bufs - 1)) + 2 * X.plan_bufs * si;
+  return X.pools[0].cur + 2 * (int)(X.k_host & (graph_ks(X) - 1)) + 2 * graph_ks(X) * si;
 }
 
 // Steps that share a launch (multi_step_kernel) where a step is one launch of
@@ -1181,16 +1237,21 @@ sbt_status capture_graph(sbt_ctx &X, int slot, int steps) {
 // Every graph size for both parities of level 0 at the current plan buffer,
 // so a long call never captures inside its run.
 sbt_status capture_all(sbt_ctx &X) {
+  const int64_t saved_k = X.k_host;
   for (int flip = 0; flip < 2; ++flip) {
-    if (flip)
+    if (flip) {  // one step on
       X.pools[0].cur ^= 1;
+      X.k_host += forcing_phases(X);
+    }
     sbt_status st = SBT_OK;
     for (int si = 0; si < 3 && !st; ++si) {
       const int slot = graph_slot(X, si);
       if (!X.graph[slot]) st = capture_graph(X, slot, kGraphSteps[si]);
     }
-    if (flip)
+    if (flip) {
       X.pools[0].cur ^= 1;
+      X.k_host = saved_k;
+    }
     if (st) return st;
   }
   return SBT_OK;
@@ -1668,6 +1729,7 @@ sbt_status sbt_synchronize(sbt_ctx *ctx) {
     if (err[0] & ERR_WINDOW) return fail(SBT_ERR_MARKER_OUTSIDE, "IBM window larger than planned");
     if (err[0] & ERR_PLAN) return fail(SBT_ERR_STATE, "IBM plan out of step with the forcing loop");
     if (err[0] & ERR_BARRIER) return fail(SBT_ERR_DEVICE, "persistent step: a grid barrier timed out");
+    if (err[0] & ERR_WAIT) return fail(SBT_ERR_DEVICE, "a collision waited for its forcing loop in vain");
   }
   return SBT_OK;
 }

@@ -191,7 +191,8 @@ struct PPhase {
 // pre-collision state) instead of streaming; READOUT = moments only, no write.
 enum : int32_t { MODE_LOCAL = 1, MODE_READOUT = 2 };
 
-enum : int32_t { ERR_NONFINITE = 1, ERR_MARKER = 2, ERR_CONTRIB = 4, ERR_WINDOW = 8, ERR_PLAN = 16, ERR_BARRIER = 32 };
+enum : int32_t { ERR_NONFINITE = 1, ERR_MARKER = 2, ERR_CONTRIB = 4, ERR_WINDOW = 8, ERR_PLAN = 16, ERR_BARRIER = 32,
+                ERR_WAIT = 64 };
 
 }  // namespace sbt
 
@@ -234,6 +235,15 @@ hipError_t sbt_launch_ibm_prep(const sbt::IbmArgs *a, hipStream_t s);
 // Multi-direct forcing loop of the current finest substep on its plan, and
 // beside it (p->n_plans > 0) the workgroups that build later substeps' plans.
 hipError_t sbt_launch_mdf(int storage, const sbt::MdfArgs *a, const sbt::IbmArgs *p, int n_bodies, hipStream_t s);
+// The forcing loops, the workgroups beside them and the tile launch of the n
+// substeps lv that follows (kpw 1, no solid blocks, no body-force sums: the
+// loops form those) as one launch.  Bodies have at most 512 markers; `odd`
+// is the lowest bit of the forcing-loop counter after this substep, for which
+// a block waits at most `spins` polls (then ERR_WAIT in err).
+hipError_t sbt_launch_mdf_level(int storage, const sbt::MdfArgs *a, const sbt::IbmArgs *p, int n_bodies, int odd,
+                                uint32_t spins, const sbt::LevelArgs *lv, int n, hipStream_t s);
+// LDS of its level workgroups (four block images and neighbour tables).
+size_t sbt_mdf_level_lds_bytes(int storage);
 // Body force F_s of the forcing loops just run, where no tile launch follows.
 hipError_t sbt_launch_body_force(const sbt::CaseDev *bodies, int n_bodies, hipStream_t s);
 size_t sbt_mdf_lds_bytes(int max_markers, int cell_cap);

@@ -1063,6 +1063,9 @@ __device__ __forceinline__ const typename Store<ST>::T *nan_src() {
   else return reinterpret_cast<const T *>(p + 4);
 }
 
+// The cell of its block a lane works on: 256 lanes to a block.
+__device__ __forceinline__ int cell_lane() { return threadIdx.x & 255; }
+
 // Issue the loads of block k into LDS image `buf`: the dense planes by
 // direct global->LDS copies (16 bytes per lane, no registers), and this
 // lane's halo population (NaN where the neighbour is missing) by a direct
@@ -1074,7 +1077,7 @@ __device__ __forceinline__ void fetch_tile(const LevelArgs &a, const Blk &k, typ
   using T = typename S::T;
   using C = typename S::C;
   using TL = Tile<ST>;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = cell_lane(), lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const T *src = static_cast<const T *>(a.src);
   const char *g = reinterpret_cast<const char *>(src + (size_t)k.self * kQ * kCells);
@@ -1111,7 +1114,7 @@ __device__ __forceinline__ void fetch_tile(const LevelArgs &a, const Blk &k, typ
 template <int ST>
 __device__ __forceinline__ void commit_tile(typename Store<ST>::T *buf, typename Store<ST>::T h, int after = 0) {
   if constexpr (!Tile<ST>::kDmaHalo) {
-    if (threadIdx.x < 188) buf[Tile<ST>::DENSE + threadIdx.x] = h;
+    if (cell_lane() < 188) buf[Tile<ST>::DENSE + cell_lane()] = h;
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
   } else {
@@ -1137,7 +1140,7 @@ __device__ __forceinline__ void compute_block(const LevelArgs &a, const CaseDev 
   // block fields are wave-uniform: keep the case parameters on the scalar
   // path (a vector load here would wait for the next block's copies)
   const CaseDev &cp = cases[__builtin_amdgcn_readfirstlane(k.cid)];
-  const int tid = threadIdx.x;
+  const int tid = cell_lane();
   const int b = __builtin_amdgcn_readfirstlane(k.self);
 
   const int x = tid & 15, y = tid >> 4;
@@ -1243,9 +1246,12 @@ __device__ __forceinline__ void compute_block(const LevelArgs &a, const CaseDev 
 // The window and counter reads are scalar, so a block outside the window
 // issues no vector load; the few blocks inside it load their cells' values
 // before the next block's copies are issued.
-template <int ST>
+// With WAIT the forcing loop runs in the same launch: a block in its window
+// waits until the loop has counted its substep (kcount's lowest bit becomes
+// `odd`), at most `spins` polls, and only then reads what it wrote.
+template <int ST, bool WAIT = false>
 __device__ __forceinline__ void ibm_force_of(const LevelArgs &a, const CaseDev *__restrict__ cases, const Blk &k,
-                                             double &fx, double &fy) {
+                                             double &fx, double &fy, int odd = 0, uint32_t spins = 0) {
   fx = 0.0;
   fy = 0.0;
   if (k.flags & BF_IBM) {
@@ -1257,11 +1263,27 @@ __device__ __forceinline__ void ibm_force_of(const LevelArgs &a, const CaseDev *
     const int x0 = __builtin_amdgcn_readfirstlane(w[0]), y0 = __builtin_amdgcn_readfirstlane(w[1]);
     const int ww = __builtin_amdgcn_readfirstlane(w[2]), wh = __builtin_amdgcn_readfirstlane(w[3]);
     if (k.ox + kB <= x0 || k.ox >= x0 + ww || k.oy + kB <= y0 || k.oy >= y0 + wh) return;
-    const int wx = k.ox + (int)(threadIdx.x & 15) - x0, wy = k.oy + (int)(threadIdx.x >> 4) - y0;
+    if constexpr (WAIT) {
+      uint32_t polls = 0;
+      while (((int)__hip_atomic_load(cp.kcount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1) != odd) {
+        if (++polls >= spins) {
+          atomicOr(a.err, ERR_WAIT);
+          return;
+        }
+        __builtin_amdgcn_s_sleep(2);
+      }
+      asm volatile("" ::: "memory");  // the loads below are issued after the one that ended the wait
+    }
+    const int wx = k.ox + (int)(threadIdx.x & 15) - x0, wy = k.oy + (cell_lane() >> 4) - y0;
     if (wx >= 0 && wx < ww && wy >= 0 && wy < wh) {
       gdbl_t *F = (gdbl_t *)cp.wF + (size_t)b * 2 * cp.win_cap + (size_t)wy * ww + wx;
-      fx = F[0];
-      fy = F[cp.win_cap];
+      if constexpr (WAIT) {  // past this XCD's L2, as it was written
+        fx = __hip_atomic_load((const double *)F, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        fy = __hip_atomic_load((const double *)F + cp.win_cap, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        fx = F[0];
+        fy = F[cp.win_cap];
+      }
     }
   }
 }
@@ -2021,11 +2043,20 @@ template <bool PAIR>
 __global__ __launch_bounds__(MDF_THREADS, 8) void ibm_prep_kernel(IbmArgs a) { prep_item<PAIR, PAIR>(a, blockIdx.x); }
 #endif
 
+// The forcing loop of substep k is done: with SHARED, blocks of the same
+// launch wait for it.
+template <bool SHARED>
+__device__ __forceinline__ void mdf_done(const CaseDev &cp, int64_t k) {
+  if constexpr (SHARED) __hip_atomic_store(cp.kcount, k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *cp.kcount = k + 1;
+}
+
+template <bool SHARED>
 __device__ __forceinline__ void mdf_fail(const CaseDev &cp, int *err, int code, int64_t k) {
   atomicOr(err, code);
   IbmWindow e = {0, 0, 0, 0};
   cp.win[k & cp.plan_mask] = e;
-  *cp.kcount = k + 1;
+  mdf_done<SHARED>(cp, k);
 }
 
 constexpr int kCellsPerLane = 4;  // stencil cells owned per lane (cell_cap <= 4096)
@@ -2070,7 +2101,9 @@ __device__ __forceinline__ void cell_weights(const uint16_t *s_list, const int *
 // over LDS with a barrier each.  A phase's loads are issued together, ahead
 // of the sums that use them in order, and what does not change in the loop
 // stays in registers.
-template <int ST, bool PAIR>
+// With SHARED the collisions that use its force are in the same launch and
+// wait for it, and F_s is summed here, while they run.
+template <int ST, bool PAIR, bool SHARED = false>
 __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
 #pragma clang fp contract(off)
   const CaseDev &cp = a.bodies[body];
@@ -2155,7 +2188,7 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
   if (!hdr.w && (hdr.x != (int)k || (k & cp.plan_mask) != b)) status = ERR_PLAN;
   if (!status && ns > cap) status = ERR_CONTRIB;
   if (status) {
-    if (tid == 0) mdf_fail(cp, a.err, status, k);
+    if (tid == 0) mdf_fail<SHARED>(cp, a.err, status, k);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // the list copies land before the LDS is released
     return;
   }
@@ -2360,31 +2393,60 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
     for (int r = 0; r < kCellsPerLane; ++r)
       if (tid + r * MDF_THREADS < ns) {
         const int wi = ((cxy[r] >> 16) - win.y0) * win.w + ((cxy[r] & 0xffff) - win.x0);
-        F[wi] = s_fx[tid + r * MDF_THREADS];
-        F[(size_t)cp.win_cap + wi] = s_fy[tid + r * MDF_THREADS];
+        if constexpr (SHARED) {
+          // to where every XCD reads it, past this one's L2: a release would
+          // write back all that the level workgroups have left in there
+          __hip_atomic_store(F + wi, s_fx[tid + r * MDF_THREADS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(F + cp.win_cap + wi, s_fy[tid + r * MDF_THREADS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          F[wi] = s_fx[tid + r * MDF_THREADS];
+          F[(size_t)cp.win_cap + wi] = s_fy[tid + r * MDF_THREADS];
+        }
       }
+  }
+#ifdef SBT_PERSISTENT_TU
+  constexpr bool kSumHere = true;  // no level launch follows to sum F_s beside
+#else
+  constexpr bool kSumHere = SHARED;
+#endif
+  if constexpr (SHARED) {
+    // every wave's part of the force density has arrived there before the
+    // count goes out
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    __syncthreads();
+    if (tid == 0) mdf_done<SHARED>(cp, k);
   }
   if (own) {
     double *gt = cp.ftot + (size_t)(k & 1) * 2 * n;
 #pragma unroll
     for (int c = 0; c < NC; ++c) gt[(comp + c) * n + m] = ft[c];
   }
-#ifdef SBT_PERSISTENT_TU
-  // the persistent step has no level launch to sum it beside: the markers'
-  // products in place of their forces of the last iteration
-  __syncthreads();
-  if (own) {
+  if constexpr (kSumHere) {
+    // the markers' products in place of their forces of the last iteration
+    if constexpr (!SHARED) __syncthreads();
+    if (own) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) reinterpret_cast<double *>(s_dF)[2 * m + comp + c] = ft[c] * dsr;
+      for (int c = 0; c < NC; ++c) reinterpret_cast<double *>(s_dF)[2 * m + comp + c] = ft[c] * dsr;
+    }
+    __syncthreads();
+    if (tid < 2) {
+      const double *v = reinterpret_cast<const double *>(s_dF) + tid;
+      double fs = 0.0;
+      int j = 0;
+      for (; j + 16 <= n; j += 16) {
+        double t[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t[r] = v[2 * (j + r)];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) fs -= t[r];
+      }
+      for (; j < n; ++j) fs -= v[2 * j];
+      cp.hist[2 * (k % cp.hist_cap) + tid] = fs;
+    }
   }
-  __syncthreads();
-  if (tid < 2) {
-    double fs = 0.0;
-    for (int j = 0; j < n; ++j) fs -= reinterpret_cast<const double *>(s_dF)[2 * j + tid];
-    cp.hist[2 * (k % cp.hist_cap) + tid] = fs;
-  }
-#endif
-  if (tid == 0) *cp.kcount = k + 1;
+  if constexpr (!SHARED)
+    if (tid == 0) mdf_done<false>(cp, k);
 }
 
 #ifndef SBT_PERSISTENT_TU
@@ -2397,6 +2459,81 @@ template <int ST, bool PAIR>
 __global__ __launch_bounds__(MDF_THREADS) void mdf_kernel(MdfArgs a, IbmArgs p, int n_bodies) {
   if ((int)blockIdx.x >= n_bodies) prep_item<16 + ST * 2 + PAIR, PAIR>(p, blockIdx.x - n_bodies);
   else mdf_body<ST, PAIR>(a, blockIdx.x);
+}
+
+// The forcing loops and the level launch that follows them as one launch of
+// 1024-lane workgroups: [0, n_bodies) run the forcing loops, then those that
+// build plans, then (from n_head, a multiple of 8, so that the XCD of a
+// workgroup is known) level workgroups of four work items, 256 lanes each.
+// Only blocks in a body's window need the forcing loop: they stage their
+// populations, wait for it, and collide; every other block runs beside it.
+// A waiting block cannot keep the loop it waits for from starting: workgroups
+// of lower index are dispatched first.
+// The loop's latency bounds it, then what follows the wait: the force density
+// goes to where every XCD reads it, and the collision of blocks already in
+// LDS.  A wing of 200 markers on 4 levels takes 113 us a step (8 such
+// launches) where forcing loops and levels apart took 137, a fixed cylinder of
+// 126 markers on 1024 x 512 cells 24.7 where they took 28.1 (F64), a cavity
+// with 402 markers 110 (114), 9 wings 167 (191).
+template <int ST>
+__global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const CaseDev *__restrict__ cases, MdfArgs m, IbmArgs p,
+                                                               int n_bodies, int n_head, int odd, uint32_t spins) {
+  using T = typename Store<ST>::T;
+  using TL = Tile<ST>;
+  const int bid = blockIdx.x;
+  if (bid < n_head) {
+    if (bid < n_bodies) mdf_body<(ST & 3), true, true>(m, bid);
+    else if (bid < n_bodies + p.n_bodies * p.n_plans) prep_item<32 + ST, true>(p, bid - n_bodies);
+    return;
+  }
+  extern __shared__ __align__(16) char lds_c[];
+  ctile_t *args = (ctile_t *)__builtin_amdgcn_kernarg_segment_ptr();
+  const int16_v hdr = *(__attribute__((address_space(4))) const int16_v *)args;
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), tid = cell_lane(), w8 = bid - n_head;
+  int seg0 = 0, w0 = 0;
+  const int item = hdr[1] ? ((w8 >> 3) * 4 + sub) << 3 | (w8 & 7) : w8 * 4 + sub;
+  const int role = __builtin_amdgcn_readfirstlane(tile_role(args, hdr, item, seg0, w0));
+  const int w = __builtin_amdgcn_readfirstlane(w0), seg = __builtin_amdgcn_readfirstlane(seg0);
+  if (role < 0) return;
+  clevel_t *lev = args->lv + seg;
+  const RunArgs r = load_run(lev);
+  const LevelArgs a = load_level(lev, r);
+  cmeta_t *meta = (cmeta_t *)r.meta;
+  ci32_t *list = (ci32_t *)r.list;
+  if (role == ROLE_BAND) {
+    const int idx = w * 256 + tid;
+    if (idx < a.n_band) band_cell<ST>(a, a.band[idx]);
+    return;
+  }
+  T *buf = reinterpret_cast<T *>(lds_c + (size_t)sub * (TL::SIZE * sizeof(T)));
+  int *cn = reinterpret_cast<int *>(lds_c + 4 * (TL::SIZE * sizeof(T))) + 36 * sub;
+  const uint32_t he = tid < 188 ? kHalo.e[tid] : 0u;
+  T h;
+  const bool slow = role == ROLE_SLOW;
+  const Blk k = load_blk(meta, list[slow ? a.n_fast + w : w]);
+  int cv = -1;
+  if (slow && (k.flags & BF_CODES) && a.fmeta && tid < 36) {
+    const int c = tid / 9, d = tid % 9;
+    const int cb = c == 0 ? k.c0 : (c == 1 ? k.c1 : (c == 2 ? k.c2 : k.c3));
+    cv = cb < 0 ? -1 : (d == 8 ? cb : a.fmeta[cb].nbr[d]);
+  }
+  fetch_tile<ST>(a, k, buf, h, he);
+  uint16_t code = 0;
+  if (slow) {
+    code = (k.flags & BF_CODES) ? a.codes[(size_t)k.code * kCells + tid] : (uint16_t)0;
+    if (tid < 36) cn[tid] = cv;
+  }
+  // the copies (and the table) have landed, for every lane of the block; the
+  // waves of band items have ended and do not count
+  if constexpr (!TL::kDmaHalo) {
+    if (tid < 188) buf[TL::DENSE + tid] = h;
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __syncthreads();
+  double fx, fy;
+  ibm_force_of<ST, true>(a, cases, k, fx, fy, odd, spins);
+  if (slow) compute_block<ST, true>(a, cases, k, buf, fx, fy, code, cn);
+  else compute_block<ST, false>(a, cases, k, buf, fx, fy);
 }
 #endif
 
@@ -2585,17 +2722,16 @@ hipError_t launch_level_st(int tile, const LevelArgs *a, hipStream_t s) {
 }  // namespace
 
 #ifndef SBT_PERSISTENT_TU
-extern "C" hipError_t sbt_launch_level_tile(int storage, const LevelArgs *lv, int n, hipStream_t s) {
+namespace {
+// Entries of a tile launch over the substeps lv[0 .. n); `groups`: its work
+// items, counting every XCD's share as the largest one with the remap.
+hipError_t tile_args(const LevelArgs *lv, int n, TileArgs &t, int &groups) {
   if (n < 1 || n > kMaxLevels) return hipErrorInvalidValue;
-  TileArgs t;
   memset(&t, 0, sizeof(t));
   t.xcd_remap = lv[0].xcd_remap;
-  bool pipe = false, solid = false;
   for (int i = 0; i < n; ++i) {
     if (lv[i].kpw < 1) return hipErrorInvalidValue;
     t.lv[i] = lv[i];
-    pipe |= lv[i].kpw > 1;
-    solid |= lv[i].n_solid > 0;
   }
   const int order[5] = {ROLE_SUM, ROLE_BAND, ROLE_SOLID, ROLE_SLOW, ROLE_RUN};
   for (int r : order)
@@ -2608,7 +2744,7 @@ extern "C" hipError_t sbt_launch_level_tile(int storage, const LevelArgs *lv, in
                                       : (a.n_fast + a.kpw - 1) / a.kpw;
       if (c > 0) t.ent[t.n_ent++] = {c, i << 3 | r};
     }
-  int groups = 0;
+  groups = 0;
   if (t.xcd_remap) {  // 8 x the largest per-XCD share (see tile_role)
     for (int x = 0; x < 8; ++x) {
       int c = 0;
@@ -2617,6 +2753,19 @@ extern "C" hipError_t sbt_launch_level_tile(int storage, const LevelArgs *lv, in
     }
   } else {
     for (int e = 0; e < t.n_ent; ++e) groups += t.ent[e].n;
+  }
+  return hipSuccess;
+}
+}  // namespace
+
+extern "C" hipError_t sbt_launch_level_tile(int storage, const LevelArgs *lv, int n, hipStream_t s) {
+  TileArgs t;
+  int groups = 0;
+  if (hipError_t e = tile_args(lv, n, t, groups)) return e;
+  bool pipe = false, solid = false;
+  for (int i = 0; i < n; ++i) {
+    pipe |= lv[i].kpw > 1;
+    solid |= lv[i].n_solid > 0;
   }
   if (groups <= 0) return hipSuccess;
   const CaseDev *cases = t.lv[0].cases;
@@ -2726,6 +2875,49 @@ extern "C" hipError_t sbt_launch_mdf(int storage, const MdfArgs *a, const IbmArg
     default: return hipErrorInvalidValue;
   }
 #undef SBT_MDF_LAUNCH
+  return hipGetLastError();
+}
+
+extern "C" size_t sbt_mdf_level_lds_bytes(int storage) {
+  return 4 * 36 * sizeof(int) +
+         4 * (size_t)((storage & 3) == 0   ? Tile<0>::SIZE * sizeof(Tile<0>::T)
+                             : (storage & 3) == 1 ? Tile<1>::SIZE * sizeof(Tile<1>::T)
+                                                  : Tile<2>::SIZE * sizeof(Tile<2>::T));
+}
+
+extern "C" hipError_t sbt_launch_mdf_level(int storage, const MdfArgs *a, const IbmArgs *p, int n_bodies, int odd,
+                                           uint32_t spins, const LevelArgs *lv, int n, hipStream_t s) {
+  TileArgs t;
+  int groups = 0;
+  if (hipError_t e = tile_args(lv, n, t, groups)) return e;
+  for (int i = 0; i < n; ++i)
+    if (lv[i].kpw != 1 || lv[i].n_solid > 0 || lv[i].n_sum > 0) return hipErrorInvalidValue;
+  if (n_bodies <= 0 || a->max_markers > MDF_THREADS / 2) return hipErrorInvalidValue;
+  const int n_prep = p->n_plans > 0 ? p->n_bodies * p->n_plans : 0;
+  size_t lds = sbt_mdf_lds_bytes(a->max_markers, a->cell_cap), l2 = sbt_mdf_level_lds_bytes(storage);
+  lds = l2 > lds ? l2 : lds;
+  if (n_prep > 0) {
+    l2 = sbt_prep_lds_bytes(p->max_markers, p->cell_cap, p->lds_window);
+    lds = l2 > lds ? l2 : lds;
+  }
+  const int n_head = (n_bodies + n_prep + 7) & ~7;
+  // with the remap items go to XCD item % 8, four of an XCD to a workgroup
+  const dim3 grid(n_head + (t.xcd_remap ? (groups / 8 + 3) / 4 * 8 : (groups + 3) / 4));
+  const CaseDev *cases = t.lv[0].cases;
+#define SBT_MDF_LEVEL(S)                                                                                          \
+  hipLaunchKernelGGL((mdf_level_kernel<S>), grid, dim3(MDF_THREADS), lds, s, t, cases, *a, *p, n_bodies, n_head, odd, spins)
+  switch (storage) {
+    case 0: SBT_MDF_LEVEL(0); break;
+    case 1: SBT_MDF_LEVEL(1); break;
+    case 2: SBT_MDF_LEVEL(2); break;
+    case 3: SBT_MDF_LEVEL(3); break;
+    case 4: SBT_MDF_LEVEL(4); break;
+    case 5: SBT_MDF_LEVEL(5); break;
+    case 6: SBT_MDF_LEVEL(6); break;
+    case 7: SBT_MDF_LEVEL(7); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef SBT_MDF_LEVEL
   return hipGetLastError();
 }
 

@@ -184,3 +184,31 @@ def test_steps_that_share_a_launch(env, storage, sizes, mrt):
         o = O.OracleSim(wls[0])
         o.step(75)
         equal_levels(many, o, wls[0])
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s", "bf16s"])
+@pytest.mark.parametrize("m,mrt,remap", [(1, False, 1), (1, True, 0), (2, True, 1), (4, False, 1), (4, True, 0)])
+def test_forcing_loops_that_share_a_launch(env, storage, m, mrt, remap):
+    """Forcing loops and the collisions that wait for them in one launch
+    against launches of their own (which the profiler times), bit for bit:
+    fixed and moving bodies, plans beside them, every part of a level, odd
+    and even counts of substeps, replayed and eager."""
+    P, O = env
+    wls = [ring(126, 20.0), ring(40, 8.0, (30.0, 90.0))]
+    if m > 1:
+        wls += [W.small_refined_flap(m=m), W.small_pitch_up(m=min(m, 3))]
+    wls = [w.replace(collision=W.COLL_MRT if mrt else W.COLL_BGK) for w in wls]
+    print(storage, m, mrt, remap, flush=True)
+    # one entry of force history: all of the state is written by the first step
+    apart, shared = P.Sim(wls, storage, history_cap=1), P.Sim(wls, storage, history_cap=1)
+    for g in (apart, shared):
+        g.set_option(P.OPT_XCD_REMAP, remap)
+    for n in (1, 2, 7, 4, 3):
+        apart.profile(n)
+        shared.step(n)
+        shared.synchronize()
+        assert np.array_equal(apart.read_state(), shared.read_state()), n
+        shared.set_option(P.OPT_GRAPH, n != 7)
+    for c in range(len(wls)):
+        a, b = np.array(apart.force_history(c, 1)), np.array(shared.force_history(c, 1))
+        assert a.shape == b.shape and a.size and np.array_equal(a, b), c
