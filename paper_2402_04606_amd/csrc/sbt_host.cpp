@@ -302,6 +302,7 @@ struct sbt_ctx {
   int cell_cap = 0;             // stencil cells per IBM plan (fits the forcing kernel's LDS)
   int plan_bufs = 1;            // IBM plan buffers per body: the finest substeps of a step
   int max_body_markers = 0;     // largest body set so far (LDS table stride)
+  int n_cu = 0;                 // compute units of the device (once a body is set)
   int64_t k_host = 0;           // finest substeps issued (every body's forcing-loop counter)
   // IBM plans beside the forcing loops: every plan_chunk-th loop's launch
   // builds plan_chunk plans ahead; 0 = none (no body moves, one plan buffer,
@@ -903,11 +904,13 @@ IbmArgs beside_args(const sbt_ctx &X) {
 // 126 markers on 512 blocks F64 19.7 / 17.1, F32 17.7 / 13.8, F16S 17.5 /
 // 13.9; on 2048 28.0 / 24.7, 20.9 / 16.4, 18.3 / 15.0; on 4608 42.1 / 40.1,
 // 28.0 / 21.8, 22.8 / 21.4; on 8192 68.5 / 71.3, 36.9 / 33.8, 28.0 / 32.8; on
-// 18432 144 / 151, 77.5 / 84.5, 40.6 / 63.0.  32 wings, the launches of up to
-// 4096 items shared: 943 / 898, 496 / 473, 347 / 338; up to 8192 of 64 wings:
-// 1675 / 1624, 862 / 839, 565 / 570.
+// 18432 144 / 151, 77.5 / 84.5, 40.6 / 63.0.  At most 16 bodies: their loops
+// take half of XCD 0's CUs; and the device must be all 8 XCDs (see
+// mdf_level_kernel).  At most 256 markers: the shared kernel's loop spills 9
+// registers, which costs a long one more than the launch saved (200 markers, 8
+// loops a step, 137 apart and 130 shared; 402 markers, 4 loops, 114 and 121).
 bool forcing_shares(const sbt_ctx &X, const Phase *ph, int n) {
-  if (X.n_bodies == 0 || X.profiling || X.max_body_markers > kMaxMarkers / 2) return false;
+  if (X.n_bodies == 0 || X.n_bodies > 16 || X.n_cu != 256 || X.profiling || X.max_body_markers > kMaxMarkers / 4) return false;
   int64_t items = 0;
   for (int i = 0; i < n; ++i) {
     const Pool &P = X.pools[ph[i].v];
@@ -1596,6 +1599,7 @@ sbt_status sbt_set_body(sbt_ctx *ctx, int32_t c, const sbt_body *body) {
     int dev = 0, lds_max = 0;
     HIPCHK(hipGetDevice(&dev));
     HIPCHK(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    HIPCHK(hipDeviceGetAttribute(&X.n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     int nmax = body->n;
     for (auto &K : X.cs) nmax = std::max(nmax, K.n_markers);
     const size_t mdf = sbt_mdf_lds_bytes(nmax, X.cell_cap), prep = sbt_prep_lds_bytes(nmax, X.cell_cap, 0);

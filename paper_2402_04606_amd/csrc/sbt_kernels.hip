@@ -12,6 +12,9 @@
 // mdf_kernel   : one workgroup per body: kinematics, moments of the stencil
 //   cells, the multi-direct-forcing loop (Eqs. (11)-(15)) and the body force
 //   (Eq. (16)), all FP64, deterministic (no floating-point atomics).
+// level_tile_kernel, mdf_level_kernel, multi_step_kernel: the launches of a
+//   step: groups of level substeps, those with the forcing loops they wait
+//   for, and several steps of a periodic level.
 //
 // Layout in HBM: per virtual level a pool of 16x16-cell blocks, SoA
 // [block][q][256] in the storage type, two lattices (read / write).
@@ -2461,20 +2464,28 @@ __global__ __launch_bounds__(MDF_THREADS) void mdf_kernel(MdfArgs a, IbmArgs p, 
   else mdf_body<ST, PAIR>(a, blockIdx.x);
 }
 
+__device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | 31 << 11) & 15; }  // XCC_ID
+
 // The forcing loops and the level launch that follows them as one launch of
-// 1024-lane workgroups: [0, n_bodies) run the forcing loops, then those that
-// build plans, then (from n_head, a multiple of 8, so that the XCD of a
-// workgroup is known) level workgroups of four work items, 256 lanes each.
-// Only blocks in a body's window need the forcing loop: they stage their
-// populations, wait for it, and collide; every other block runs beside it.
-// A waiting block cannot keep the loop it waits for from starting: workgroups
-// of lower index are dispatched first.
+// 1024-lane workgroups: of every eight of the first 8 n_bodies, one on each
+// XCD, the one on XCD 0 runs a forcing loop, the others there (and after them,
+// if need be) build plans, then (from
+// n_head, a multiple of 8, so that the XCD of a workgroup is known) level
+// workgroups of four work items, 256 lanes each.  Only blocks in a body's
+// window need the forcing loop: they stage their populations, wait for it,
+// and collide; every other block runs beside it.
+// A waiting block cannot keep the loop it waits for from starting, nor one of
+// another launch on another stream: an XCD takes a launch's workgroups in
+// order, and all loops of all launches run on XCD 0, so where a level
+// workgroup holds a CU of XCD 0, its own launch's loops have started, and they
+// end without waiting for anything.  (Which XCD takes workgroup 0 differs
+// between hardware queues, so workgroups ask which one they are on.)
 // The loop's latency bounds it, then what follows the wait: the force density
 // goes to where every XCD reads it, and the collision of blocks already in
-// LDS.  A wing of 200 markers on 4 levels takes 113 us a step (8 such
+// LDS.  A wing of 200 markers on 4 levels takes 130 us a step (8 such
 // launches) where forcing loops and levels apart took 137, a fixed cylinder of
-// 126 markers on 1024 x 512 cells 24.7 where they took 28.1 (F64), a cavity
-// with 402 markers 110 (114), 9 wings 167 (191).
+// 126 markers on 1024 x 512 cells 24.7 where they took 28.1 (F64), 9 wings 182
+// (191).
 template <int ST>
 __global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const CaseDev *__restrict__ cases, MdfArgs m, IbmArgs p,
                                                                int n_bodies, int n_head, int odd, uint32_t spins) {
@@ -2482,8 +2493,12 @@ __global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const 
   using TL = Tile<ST>;
   const int bid = blockIdx.x;
   if (bid < n_head) {
-    if (bid < n_bodies) mdf_body<(ST & 3), true, true>(m, bid);
-    else if (bid < n_bodies + p.n_bodies * p.n_plans) prep_item<32 + ST, true>(p, bid - n_bodies);
+    // loops first, then plans
+    const int x = xcd_id();
+    int job = bid >= 8 * n_bodies ? bid : (x == 0 ? bid >> 3 : n_bodies + (bid >> 3) * 7 + x - 1);
+    asm volatile("" : "+s"(job));  // known parts of it would cost the loop registers
+    if (job < n_bodies) mdf_body<(ST & 3), true, true>(m, job);
+    else if (job < n_bodies + p.n_bodies * p.n_plans) prep_item<32 + ST, true>(p, job - n_bodies);
     return;
   }
   extern __shared__ __align__(16) char lds_c[];
@@ -2900,7 +2915,7 @@ extern "C" hipError_t sbt_launch_mdf_level(int storage, const MdfArgs *a, const 
     l2 = sbt_prep_lds_bytes(p->max_markers, p->cell_cap, p->lds_window);
     lds = l2 > lds ? l2 : lds;
   }
-  const int n_head = (n_bodies + n_prep + 7) & ~7;
+  const int n_head = 8 * n_bodies + ((n_prep > 7 * n_bodies ? n_prep - 7 * n_bodies : 0) + 7) / 8 * 8;
   // with the remap items go to XCD item % 8, four of an XCD to a workgroup
   const dim3 grid(n_head + (t.xcd_remap ? (groups / 8 + 3) / 4 * 8 : (groups + 3) / 4));
   const CaseDev *cases = t.lv[0].cases;
