@@ -2484,8 +2484,7 @@ __device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | 
 // goes to where every XCD reads it, and the collision of blocks already in
 // LDS.  A wing of 200 markers on 4 levels takes 130 us a step (8 such
 // launches) where forcing loops and levels apart took 137, a fixed cylinder of
-// 126 markers on 1024 x 512 cells 24.7 where they took 28.1 (F64), 9 wings 182
-// (191).
+// 126 markers on 1024 x 512 cells 24.7 where they took 28.1 (F64).
 template <int ST>
 __global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const CaseDev *__restrict__ cases, MdfArgs m, IbmArgs p,
                                                                int n_bodies, int n_head, int odd, uint32_t spins) {
