@@ -34,7 +34,9 @@ hipError_t HostCopy::to_host(const Piece *p, int n, hipStream_t s) {
   size_t total = 0;
   for (int i = 0; i < n; ++i) total += p[i].bytes;
   int dev = 0;
-  if (total < kLarge || !ready() || hipGetDevice(&dev) != hipSuccess) {
+  // the per-thread stream is another one in each worker, which would not wait
+  // for what the caller's holds: the caller copies by itself
+  if (total < kLarge || s == hipStreamPerThread || !ready() || hipGetDevice(&dev) != hipSuccess) {
     for (int i = 0; i < n; ++i) {
       const hipError_t e = hipMemcpyAsync(p[i].host, p[i].dev, p[i].bytes, hipMemcpyDeviceToHost, s);
       if (e != hipSuccess) return e;

@@ -12,7 +12,8 @@ namespace sbt {
 // caller's among them) each take pieces of kChunk bytes in turn through a
 // pinned buffer of their own, so one's copy out overlaps the others'
 // transfers.  Buffers are made at the first large copy and freed with the
-// object; without them, or below kLarge bytes, the runtime copies.
+// object; without them, below kLarge bytes, or on the per-thread stream the
+// runtime copies.
 class HostCopy {
  public:
   struct Piece {
