@@ -1104,22 +1104,33 @@ __device__ __forceinline__ void fetch_tile(const LevelArgs &a, const Blk &k, typ
   }
 }
 
-// Make buf complete for every lane: this lane's halo value (8-byte
-// storage), then wait for this wave's direct copies before the barrier
-// (other waves read them).  Vector memory operations complete in issue
-// order, so when at least `after` were issued after this buffer's copies
-// (later blocks' copies, earlier blocks' 9 stores), vmcnt(after) covers the
-// copies without waiting for those.  The barrier then carries no memory fence: a fence
-// would wait for the stores too.  Only LDS is shared across it, and every
-// LDS access before it has completed (the copies by the wait, the reads
-// because their values were used); the empty asm statements keep the
-// compiler from moving memory accesses across it.
+// Make buf, and whatever else the lanes have stored to LDS, complete for
+// every lane: this lane's halo value (8-byte storage), this wave's direct
+// copies, every store.
+template <int ST>
+__device__ __forceinline__ void commit_stores(typename Store<ST>::T *buf, typename Store<ST>::T h) {
+  if constexpr (!Tile<ST>::kDmaHalo) {
+    if (cell_lane() < 188) buf[Tile<ST>::DENSE + cell_lane()] = h;
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __syncthreads();
+}
+
+// Make buf complete for every lane where the lanes have stored nothing else
+// to LDS (an interior block).  8-byte storage stores its halo and waits for
+// everything; otherwise this wave's direct copies are all there is to wait
+// for before the barrier (other waves read them).  Vector memory operations
+// complete in issue order, so when at least `after` were issued after this
+// buffer's copies (later blocks' copies, earlier blocks' 9 stores),
+// vmcnt(after) covers the copies without waiting for those.  The barrier then
+// carries no memory fence: a fence would wait for the stores too.  Only LDS is
+// shared across it, and every LDS access before it has completed (the copies
+// by the wait, the reads because their values were used); the empty asm
+// statements keep the compiler from moving memory accesses across it.
 template <int ST>
 __device__ __forceinline__ void commit_tile(typename Store<ST>::T *buf, typename Store<ST>::T h, int after = 0) {
   if constexpr (!Tile<ST>::kDmaHalo) {
-    if (cell_lane() < 188) buf[Tile<ST>::DENSE + cell_lane()] = h;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __syncthreads();
+    commit_stores<ST>(buf, h);
   } else {
     // vmcnt(n) with lgkmcnt and expcnt left at their maxima
     if (after >= 9) __builtin_amdgcn_s_waitcnt(0x0F79);        // vmcnt(9)
@@ -1539,7 +1550,7 @@ __global__ __launch_bounds__(256) void level_tile_kernel(TileArgs, const CaseDev
     const uint16_t code = (k.flags & BF_CODES) ? a.codes[(size_t)k.code * kCells + threadIdx.x] : (uint16_t)0;
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the table entry (and the copies) have landed
     if (threadIdx.x < 36) cn[threadIdx.x] = cv;
-    commit_tile<ST>(bufA, h);
+    commit_stores<ST>(bufA, h);
     compute_block<ST, true>(a, cases, k, bufA, fx, fy, code, cn);
   } else if (role == ROLE_BAND) {
     int idx = w * 256 + threadIdx.x;
@@ -2537,13 +2548,8 @@ __global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const 
     code = (k.flags & BF_CODES) ? a.codes[(size_t)k.code * kCells + tid] : (uint16_t)0;
     if (tid < 36) cn[tid] = cv;
   }
-  // the copies (and the table) have landed, for every lane of the block; the
-  // waves of band items have ended and do not count
-  if constexpr (!TL::kDmaHalo) {
-    if (tid < 188) buf[TL::DENSE + tid] = h;
-  }
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  __syncthreads();
+  // the waves of band items have ended and do not count
+  commit_stores<ST>(buf, h);
   double fx, fy;
   ibm_force_of<ST, true>(a, cases, k, fx, fy, odd, spins);
   if (slow) compute_block<ST, true>(a, cases, k, buf, fx, fy, code, cn);
