@@ -89,7 +89,7 @@ struct alignas(16) CaseDev {
                                // 1 if the plan serves every substep (fixed body)
   double *wF;                  // [plan_mask + 1][2][win_cap] force density in the window, per plan buffer
   int32_t *wCnt, *wIdx;        // [plan_mask + 1][win_cap] plan builder's counters / compact index beyond LDS
-  int32_t *p_ij;               // [plan_mask + 1][2 nm_cap] first tap of each marker (x | y << 16; half of it used)
+  int32_t *p_ij;               // [plan_mask + 1][2 nm_cap] first tap of each marker in the window (x | y << 16; half of it used)
   double *p_w;                 // [plan_mask + 1][nm_cap][8] Peskin weights of the 4 x and 4 y taps
   double *p_ud;                // [plan_mask + 1][2][nm_cap] desired marker velocity
   uint16_t *p_tap;             // [plan_mask + 1][nm_cap][16] stencil cell of each tap

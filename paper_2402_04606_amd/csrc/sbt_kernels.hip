@@ -1705,12 +1705,13 @@ __device__ __forceinline__ void sort_net(int (&v)[N]) {
 
 // Plan buffer b of a case: element offsets of its arrays.
 struct PlanView {
-  int32_t *ij;           // [nm] first tap of each marker, x | y << 16
+  int32_t *ij;           // [nm] first tap of each marker in the window, x | y << 16
   double *w;             // [nm][8]: wx[0..3], wy[0..3]
   double *ud;            // [2][nm]: desired velocity (x, y)
   uint16_t *tap;         // [nm][16]: stencil cell (place q) of each tap (y outer, x inner)
-  int32_t *cell;         // [cell_cap][8]: gather record of place g: 4 source blocks, x | y << 16, place q;
-                         //   spread record of place q: csr start | count << 16, x | y << 16
+  int32_t *cell;         // [cell_cap][8]: gather record of place g: 4 source blocks, x | y << 16 (of each the
+                         //   low 16 bits, which place it in its blocks), place q;
+                         //   spread record of place q: csr start | count << 16, x | y << 16 in the window
   uint16_t *list;        // [16 nm]: contributors of the stencil cells, CSR
   int32_t *hdr;          // [4]: stamp (low 32 bits of k), stencil cells, status, serves every substep
 };
@@ -1867,12 +1868,11 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
     }
   }
   const int i0 = t0[0], j0 = t0[1];
-  if (own && ax == 0) P.ij[m] = (i0 & 0xffff) | (j0 << 16);
   __syncthreads();
   const int wx0 = s_box[0], wy0 = s_box[1];
   const int ww = s_box[2] - wx0, wh = s_box[3] - wy0;
-  const int ncell = ww * wh;
-  if (ncell > cp.win_cap || ww <= 0 || wh <= 0) {
+  // places in the window are kept in 16 bits per axis
+  if (ww <= 0 || wh <= 0 || ww > 65535 || wh > 65535 || (int64_t)ww * wh > cp.win_cap) {
     if (tid == 0) {
       IbmWindow e = {0, 0, 0, 0};
       cp.win[b] = e;
@@ -1880,6 +1880,8 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
     put_header(0, ERR_WINDOW);
     return;
   }
+  const int ncell = ww * wh;
+  if (own && ax == 0) P.ij[m] = (i0 - wx0) | ((j0 - wy0) << 16);
   if (tid == 0) {
     IbmWindow w = {wx0, wy0, ww, wh};
     cp.win[b] = w;
@@ -1998,7 +2000,7 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
     if (sw < 0 || se < 0 || nw < 0 || ne < 0) s_bad = 1;
     int32_t *R = P.cell + (size_t)g * 8;
     *reinterpret_cast<int4 *>(R) = make_int4(sw, se, nw, ne);
-    *reinterpret_cast<int2 *>(R + 4) = make_int2(gx | (gy << 16), q);
+    *reinterpret_cast<int2 *>(R + 4) = make_int2((gx & 0xffff) | (gy << 16), q);
   }
   __syncthreads();
   // 5. fill the contributor lists (slot order is arbitrary) and the
@@ -2021,8 +2023,8 @@ __device__ __forceinline__ void prep_item(const IbmArgs a, unsigned item) {
   for (int q = tid; q < ns; q += MDF_THREADS) {
     const int c = s_cells[q];
     const int n_c = count_of(c), st = s_start[q];
-    const int cy = c / ww, gx = wx0 + c - cy * ww, gy = wy0 + cy;
-    *reinterpret_cast<int2 *>(P.cell + (size_t)q * 8 + 6) = make_int2(st | (n_c << 16), gx | (gy << 16));
+    const int cy = c / ww, cx = c - cy * ww;
+    *reinterpret_cast<int2 *>(P.cell + (size_t)q * 8 + 6) = make_int2(st | (n_c << 16), cx | (cy << 16));
     uint16_t *L = s_list + st;
     uint16_t *O = P.list + st;
     // the wave's first cell has its largest count
@@ -2083,7 +2085,7 @@ __device__ __forceinline__ int corner_block(int gx, int gy, int sx, int sy, int 
   return west ? (south ? sw : nw) : (south ? se : ne);
 }
 
-// Contributors [e0, e0 + 4) of a stencil cell at (gx, gy) whose list starts
+// Contributors [e0, e0 + 4) of the window's cell (gx, gy) whose list starts
 // at st: the markers' indices and the weights w_x w_y.  Every load of a kind
 // is issued before the next kind needs it.  Past the last contributor (cnt)
 // it is repeated with weight 0: adding a product of 0 leaves the sum as it
@@ -2220,7 +2222,7 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
   const int l = cp.n_levels - 1;
   //    (the lane gathers the cell in place tid of the gather order and
   //    spreads to the one in place tid of the order by count)
-  int cxy[kCellsPerLane], csc[kCellsPerLane];  // gx | gy << 16, list start | count << 16
+  int cxy[kCellsPerLane], csc[kCellsPerLane];  // x | y << 16 in the window, list start | count << 16
 #pragma unroll
   for (int r0 = 0; r0 < kCellsPerLane; r0 += 2) {
     typename Store<ST>::T g[2][9];
@@ -2406,7 +2408,7 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
 #pragma unroll
     for (int r = 0; r < kCellsPerLane; ++r)
       if (tid + r * MDF_THREADS < ns) {
-        const int wi = ((cxy[r] >> 16) - win.y0) * win.w + ((cxy[r] & 0xffff) - win.x0);
+        const int wi = (int)((uint32_t)cxy[r] >> 16) * win.w + (cxy[r] & 0xffff);
         if constexpr (SHARED) {
           // to where every XCD reads it, past this one's L2: a release would
           // write back all that the level workgroups have left in there

@@ -212,3 +212,38 @@ def test_forcing_loops_that_share_a_launch(env, storage, m, mrt, remap):
     for c in range(len(wls)):
         a, b = np.array(apart.force_history(c, 1)), np.array(shared.force_history(c, 1))
         assert a.shape == b.shape and a.size and np.array_equal(a, b), c
+
+
+@pytest.mark.parametrize("bodies_share", [True, False])
+def test_bodies_far_from_the_origin(env, bodies_share):
+    """A ring under six levels of a periodic plane, moved to finest cells
+    beyond 32768 in y and beyond 65536 in x by whole level-0 blocks: marker
+    positions are exact in both places, so every bit of the run moves along."""
+    P, O = env
+    m, r = 6, 8.0
+
+    def placed(kx, ky):
+        wl = nest(m, False)
+        ring40 = ring(40, r).body
+        xb, yb = (np.round(np.asarray(v) * 4096.0) / 4096.0 for v in (ring40.xb, ring40.yb))
+        boxes = [(l, x0 + (kx << l), y0 + (ky << l), x1 + (kx << l), y1 + (ky << l)) for l, x0, y0, x1, y1 in wl.boxes]
+        p = [1024.25 + 512 * kx, 1024.25 + 512 * ky] + [0.0] * 14
+        return wl.replace(nx0=16 * 133, ny0=16 * 69, boxes=boxes, init=W.uniform_init(1.0, 0.05, 0.01),
+                          body=W.Body(W.BODY_FIXED, xb, yb, ring40.ds, p))
+
+    def run(kx, ky):
+        print(kx, ky, bodies_share, flush=True)
+        g = P.Sim(placed(kx, ky), "f64")
+        if bodies_share:
+            g.step(2)
+        else:
+            g.profile(2)
+        g.synchronize()
+        return np.array(g.force_history(0)), [np.roll(f, (-16 * ky, -16 * kx), (0, 1)) for f in g.fields(0, 0)]
+
+    h0, f0 = run(0, 0)
+    assert np.isfinite(h0).all() and np.abs(h0).max() > 0
+    for at in ((0, 65), (129, 0), (129, 65)):
+        h, f = run(*at)
+        assert np.array_equal(h, h0), at
+        assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(f, f0)), at
