@@ -239,9 +239,10 @@ hipError_t sbt_launch_mdf(int storage, const sbt::MdfArgs *a, const sbt::IbmArgs
 // substeps lv that follows (kpw 1, no solid blocks, no body-force sums: the
 // loops form those) as one launch.  Bodies have at most 512 markers; `odd`
 // is the lowest bit of the forcing-loop counter after this substep, for which
-// a block waits at most `spins` polls (then ERR_WAIT in err).
+// a block waits at most `spins` polls (then ERR_WAIT in err); `tickets` is a
+// word of device memory, zero between launches.
 hipError_t sbt_launch_mdf_level(int storage, const sbt::MdfArgs *a, const sbt::IbmArgs *p, int n_bodies, int odd,
-                                uint32_t spins, const sbt::LevelArgs *lv, int n, hipStream_t s);
+                                uint32_t spins, uint32_t *tickets, const sbt::LevelArgs *lv, int n, hipStream_t s);
 // LDS of its level workgroups (four block images and neighbour tables).
 size_t sbt_mdf_level_lds_bytes(int storage);
 // Body force F_s of the forcing loops just run, where no tile launch follows.

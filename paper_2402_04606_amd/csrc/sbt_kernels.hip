@@ -2201,7 +2201,7 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
   const int ns = hdr.y;
   int status = hdr.z;
   // a fixed body's plan serves every substep
-  if (!hdr.w && (hdr.x != (int)k || (k & cp.plan_mask) != b)) status = ERR_PLAN;
+  if ((!hdr.w && hdr.x != (int)k) || (k & cp.plan_mask) != b) status = ERR_PLAN;
   if (!status && ns > cap) status = ERR_CONTRIB;
   if (status) {
     if (tid == 0) mdf_fail<SHARED>(cp, a.err, status, k);
@@ -2477,22 +2477,22 @@ __global__ __launch_bounds__(MDF_THREADS) void mdf_kernel(MdfArgs a, IbmArgs p, 
   else mdf_body<ST, PAIR>(a, blockIdx.x);
 }
 
-__device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | 31 << 11) & 15; }  // XCC_ID
-
 // The forcing loops and the level launch that follows them as one launch of
-// 1024-lane workgroups: of every eight of the first 8 n_bodies, one on each
-// XCD, the one on XCD 0 runs a forcing loop, the others there (and after them,
-// if need be) build plans, then (from
-// n_head, a multiple of 8, so that the XCD of a workgroup is known) level
+// 1024-lane workgroups: n_head (a multiple of 8, so that the XCD of those
+// behind is known) that take a number each as they start, and of those the
+// first n_bodies run a forcing loop and the next build a plan; then level
 // workgroups of four work items, 256 lanes each.  Only blocks in a body's
 // window need the forcing loop: they stage their populations, wait for it,
 // and collide; every other block runs beside it.
+// The numbers come from a counter, so each loop runs once wherever the
+// workgroups land, and the last to take one sets it back for the next launch.
 // A waiting block cannot keep the loop it waits for from starting, nor one of
-// another launch on another stream: an XCD takes a launch's workgroups in
-// order, and all loops of all launches run on XCD 0, so where a level
-// workgroup holds a CU of XCD 0, its own launch's loops have started, and they
-// end without waiting for anything.  (Which XCD takes workgroup 0 differs
-// between hardware queues, so workgroups ask which one they are on.)
+// another launch on another stream: an XCD starts its share of a launch's
+// workgroups in order, and of the 8 n_bodies or more at the head every XCD has
+// at least n_bodies, so where a level workgroup holds a CU, as many of its
+// launch's head have started on that XCD alone as there are loops, all loops
+// are taken by workgroups that hold a CU, and those end without waiting for
+// anything.
 // The loop's latency bounds it, then what follows the wait: the force density
 // goes to where every XCD reads it, and the collision of blocks already in
 // LDS.  A wing of 200 markers on 4 levels takes 130 us a step (8 such
@@ -2500,14 +2500,20 @@ __device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | 
 // 126 markers on 1024 x 512 cells 24.7 where they took 28.1 (F64).
 template <int ST>
 __global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const CaseDev *__restrict__ cases, MdfArgs m, IbmArgs p,
-                                                               int n_bodies, int n_head, int odd, uint32_t spins) {
+                                                               int n_bodies, int n_head, int odd, uint32_t spins,
+                                                               uint32_t *tickets) {
   using T = typename Store<ST>::T;
   using TL = Tile<ST>;
   const int bid = blockIdx.x;
   if (bid < n_head) {
-    // loops first, then plans
-    const int x = xcd_id();
-    int job = bid >= 8 * n_bodies ? bid : (x == 0 ? bid >> 3 : n_bodies + (bid >> 3) * 7 + x - 1);
+    __shared__ int s_job;
+    if (threadIdx.x == 0) {
+      const int t = (int)__hip_atomic_fetch_add(tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (t == n_head - 1) __hip_atomic_store(tickets, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_job = t;
+    }
+    __syncthreads();
+    int job = __builtin_amdgcn_readfirstlane(s_job);
     asm volatile("" : "+s"(job));  // known parts of it would cost the loop registers
     if (job < n_bodies) mdf_body<(ST & 3), true, true>(m, job);
     else if (job < n_bodies + p.n_bodies * p.n_plans) prep_item<32 + ST, true>(p, job - n_bodies);
@@ -2908,7 +2914,7 @@ extern "C" size_t sbt_mdf_level_lds_bytes(int storage) {
 }
 
 extern "C" hipError_t sbt_launch_mdf_level(int storage, const MdfArgs *a, const IbmArgs *p, int n_bodies, int odd,
-                                           uint32_t spins, const LevelArgs *lv, int n, hipStream_t s) {
+                                           uint32_t spins, uint32_t *tickets, const LevelArgs *lv, int n, hipStream_t s) {
   TileArgs t;
   int groups = 0;
   if (hipError_t e = tile_args(lv, n, t, groups)) return e;
@@ -2923,11 +2929,12 @@ extern "C" hipError_t sbt_launch_mdf_level(int storage, const MdfArgs *a, const 
     lds = l2 > lds ? l2 : lds;
   }
   const int n_head = 8 * n_bodies + ((n_prep > 7 * n_bodies ? n_prep - 7 * n_bodies : 0) + 7) / 8 * 8;
+  if (!tickets) return hipErrorInvalidValue;
   // with the remap items go to XCD item % 8, four of an XCD to a workgroup
   const dim3 grid(n_head + (t.xcd_remap ? (groups / 8 + 3) / 4 * 8 : (groups + 3) / 4));
   const CaseDev *cases = t.lv[0].cases;
 #define SBT_MDF_LEVEL(S)                                                                                          \
-  hipLaunchKernelGGL((mdf_level_kernel<S>), grid, dim3(MDF_THREADS), lds, s, t, cases, *a, *p, n_bodies, n_head, odd, spins)
+  hipLaunchKernelGGL((mdf_level_kernel<S>), grid, dim3(MDF_THREADS), lds, s, t, cases, *a, *p, n_bodies, n_head, odd, spins, tickets)
   switch (storage) {
     case 0: SBT_MDF_LEVEL(0); break;
     case 1: SBT_MDF_LEVEL(1); break;

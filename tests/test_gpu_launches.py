@@ -247,3 +247,40 @@ def test_bodies_far_from_the_origin(env, bodies_share):
         h, f = run(*at)
         assert np.array_equal(h, h0), at
         assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(f, f0)), at
+
+
+@pytest.mark.parametrize("m", [5, 6])
+def test_plans_behind_a_single_loop(env, m):
+    """One moving body on 5 and 6 levels: 8 and 16 plans beside one loop, more
+    than the first eight workgroups of a launch take."""
+    P, O = env
+    wl = W.small_refined_flap(m=m)
+    print(wl.name, flush=True)
+    apart, shared = P.Sim(wl, "f32", history_cap=1), P.Sim(wl, "f32", history_cap=1)
+    for n in (1, 3, 4):
+        apart.profile(n)
+        shared.step(n)
+        shared.synchronize()
+        assert np.array_equal(apart.read_state(), shared.read_state()), n
+
+
+def test_contexts_on_two_streams(env):
+    """Two contexts, each with several bodies and more level workgroups than
+    the chip holds at once, step at the same time on streams of their own: the
+    blocks of one that wait never keep the other's loops from running."""
+    import torch
+    P, O = env
+    a = [ring(126, 20.0, (150.0, 256.0), 1024, 512), ring(40, 8.0, (30.0, 90.0))]
+    b = [W.small_refined_flap(m=4), ring(200, 24.0, (200.0, 256.0), 1024, 512)]
+    refs = [P.Sim(w, "f32", history_cap=1) for w in (a, b)]
+    for g in refs:
+        g.step(120)
+        g.synchronize()
+    both = [P.Sim(w, "f32", history_cap=1, stream=torch.cuda.Stream()) for w in (a, b)]
+    for n in range(30):
+        for g in both:
+            g.step(4)
+    print("issued", flush=True)
+    for g, ref in zip(both, refs):
+        g.synchronize()
+        assert np.array_equal(g.read_state(), ref.read_state())
