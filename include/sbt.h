@@ -327,9 +327,15 @@ sbt_status sbt_write_state(sbt_ctx *ctx, const void *host, size_t bytes);
  *   launch sizes its grid to fill every CU, so kernels of other streams
  *   running at the same time can keep a workgroup from starting and make a
  *   barrier time out.
- * SBT_OPT_BARRIER_SPINS: polls a grid-barrier wait of the persistent step
- *   makes before it gives up; 0 (default) = 2^21 (about a second).  A small
- *   value forces the time-out path (for tests of it). */
+ * SBT_OPT_BARRIER_SPINS: polls that a wait inside a launch makes before it
+ *   gives up; 0 (default) = 2^21 (about a second).  A small value forces the
+ *   time-out path (for tests of it).  Two kinds of launch wait: the persistent
+ *   step at its grid barriers, and, where forcing loops share a launch with the
+ *   collisions that follow them, a block in a body's window for that body's
+ *   loop.  The loop it waits for has always started, whatever else the device
+ *   runs, so the default does not give up.  A block that does collides without
+ *   the body's force: sbt_synchronize then reports SBT_ERR_DEVICE (the
+ *   readouts do not look), and the state is not a result. */
 enum { SBT_OPT_GRAPH = 0, SBT_OPT_TILE = 1, SBT_OPT_XCD_REMAP = 2, SBT_OPT_PERSISTENT = 3, SBT_OPT_BARRIER_SPINS = 4 };
 sbt_status sbt_set_option(sbt_ctx *ctx, int32_t option, int32_t value);
 /* Pick the blocks per workgroup of each level by timing `steps` steps per

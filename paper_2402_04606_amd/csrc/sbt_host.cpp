@@ -294,7 +294,7 @@ struct sbt_ctx {
   std::vector<int> ptab_n;
   uint32_t *d_bar = nullptr;       // [4] grid-barrier state of the persistent step; job counter of the shared forcing launches
   int p_groups = 0;                // its workgroups (0: not sized yet)
-  uint32_t p_spins = kBarrierSpins;  // polls of a grid-barrier wait before it gives up
+  uint32_t p_spins = kBarrierSpins;  // polls of a wait inside a launch before it gives up
   size_t p_lds = 0;
   std::vector<int> kpw_level;   // interior blocks per workgroup per virtual level (0: automatic)
   int lds_window = 0;           // IBM window cells whose plan-builder counters fit in LDS
@@ -929,7 +929,7 @@ sbt_status launch_forcing_shared(sbt_ctx &X, const Phase *ph, int n, hipStream_t
   LevelArgs lv[kMaxLevels];
   substep_args(X, ph, n, false, lv);
   for (int i = 0; i < n; ++i) lv[i].kpw = 1;
-  HIPCHK(sbt_launch_mdf_level(X.kvar, &a, &p, X.n_bodies, (int)(X.k_host & 1), kBarrierSpins, X.d_bar + 3, lv, n, s));
+  HIPCHK(sbt_launch_mdf_level(X.kvar, &a, &p, X.n_bodies, (int)(X.k_host & 1), X.p_spins, X.d_bar + 3, lv, n, s));
   return SBT_OK;
 }
 

@@ -264,6 +264,33 @@ def test_plans_behind_a_single_loop(env, m):
         assert np.array_equal(apart.read_state(), shared.read_state()), n
 
 
+def test_a_wait_that_gives_up_is_reported(env):
+    """One poll per wait (set from the host): the launch ends normally,
+    synchronize reports it once, and after write_state with the default limit
+    the context steps as one that never gave up."""
+    P, O = env
+    wl = ring(126, 20.0)
+    print(wl.name, flush=True)
+    # one entry of force history: all of the state is written by the first step
+    g, ref = P.Sim(wl, "f64", history_cap=1), P.Sim(wl, "f64", history_cap=1)
+    for s in (g, ref):
+        s.step(5)
+        s.synchronize()
+    state = g.read_state()
+    g.set_option(P.OPT_BARRIER_SPINS, 1)
+    g.step(2)
+    with pytest.raises(P.SbtError) as e:
+        g.synchronize()
+    assert e.value.code == -3
+    g.synchronize()
+    g.set_option(P.OPT_BARRIER_SPINS, 0)
+    g.write_state(state)
+    for s in (g, ref):
+        s.step(6)
+        s.synchronize()
+    assert np.array_equal(g.read_state(), ref.read_state())
+
+
 def test_contexts_on_two_streams(env):
     """Two contexts, each with several bodies and more level workgroups than
     the chip holds at once, step at the same time on streams of their own: the
