@@ -2582,7 +2582,11 @@ __global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const 
 // Grid barrier number `idx` (1, 2, ...) of the launch: bar[0] counts
 // arrivals, so it is passed when bar[0] >= idx * gridDim.x.  The release
 // makes this workgroup's writes visible at agent scope and the acquire
-// invalidates what this CU cached before.  A wait of `spins` polls without
+// invalidates what this CU cached before: once, after the last poll.  A poll
+// that acquires invalidates the caches of its whole XCD under the workgroups
+// still at work, and with 255 of them polling beside one forcing loop, a step
+// of one wing on 4 levels took 878 us where it takes 461 (F32), the 64-case
+// batch 2502 where it takes 2075 (F16S).  A wait of `spins` polls without
 // the barrier passing raises ERR_BARRIER and sets bar[1], which ends every
 // other wait.  Returns false when the launch is aborted.
 __device__ bool grid_barrier(uint32_t *bar, uint32_t idx, int32_t *err, uint32_t spins_max) {
@@ -2593,7 +2597,7 @@ __device__ bool grid_barrier(uint32_t *bar, uint32_t idx, int32_t *err, uint32_t
     __hip_atomic_fetch_add(&bar[0], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t target = idx * gridDim.x;
     uint32_t spins = 0;
-    while (__hip_atomic_load(&bar[0], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
+    while (__hip_atomic_load(&bar[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
       if (__hip_atomic_load(&bar[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
         ok = 0;
         break;
@@ -2606,6 +2610,7 @@ __device__ bool grid_barrier(uint32_t *bar, uint32_t idx, int32_t *err, uint32_t
       }
       __builtin_amdgcn_s_sleep(2);
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     s_ok = ok;
   }
   __syncthreads();
@@ -2634,6 +2639,20 @@ __device__ __forceinline__ void level_phase(const PPhase &P) {
   }
 }
 
+// The plan builder and the forcing loop as functions, called only by the
+// workgroups that have an item: inlined beside the level path they cost all of
+// them spills (165 VGPRs in F64, 78 now; 512^2 cells without a body 42 us a
+// step inlined, 29 as functions), while a call saves and restores registers.
+template <int ST>
+__device__ __attribute__((noinline)) void prep_phase(const PPhase *P, unsigned item) {
+  prep_item<64 + ST, false>(P->ibm, item);
+}
+
+template <int ST>
+__device__ __attribute__((noinline)) void mdf_phase(const PPhase *P, unsigned item) {
+  mdf_body<ST & 3, false>(P->mdf, item);
+}
+
 template <int ST>
 __global__ __launch_bounds__(MDF_THREADS) void step_persistent_kernel(const PPhase *__restrict__ ph, int n_ph,
                                                                       uint32_t *bar, int32_t *err, uint32_t spins) {
@@ -2642,12 +2661,12 @@ __global__ __launch_bounds__(MDF_THREADS) void step_persistent_kernel(const PPha
     const PPhase &P = ph[p];
     if (P.type == PP_PREP) {
       for (unsigned it = blockIdx.x; it < (unsigned)P.n_items; it += gridDim.x) {
-        prep_item<2, false>(P.ibm, it);
+        prep_phase<ST>(&P, it);
         __syncthreads();
       }
     } else if (P.type == PP_MDF) {
       for (unsigned it = blockIdx.x; it < (unsigned)P.n_items; it += gridDim.x) {
-        mdf_body<ST & 3, false>(P.mdf, it);
+        mdf_phase<ST>(&P, it);
         __syncthreads();
       }
     } else {
