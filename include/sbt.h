@@ -315,7 +315,9 @@ sbt_status sbt_write_state(sbt_ctx *ctx, const void *host, size_t bytes);
  *   steps; all are captured at the first step that uses one).
  * SBT_OPT_TILE: interior 16x16 blocks per workgroup of the stream+collide
  *   launch, 1..16 for every level (a workgroup loads block j+1 while it
- *   computes block j); 0 (default) = automatic per launch size.
+ *   computes block j); 0 (default) = automatic per launch size.  Launches of
+ *   several steps (calls of more than 4 steps on a single periodic level
+ *   without bodies and solid cells) take one block per workgroup always.
  * SBT_OPT_XCD_REMAP (default 1): map consecutive Morton blocks to one XCD.
  * SBT_OPT_PERSISTENT (default 0): run each step as one persistent launch
  *   (plan builder, forcing loops and level substeps as phases separated by
@@ -341,8 +343,9 @@ sbt_status sbt_set_option(sbt_ctx *ctx, int32_t option, int32_t value);
 /* Pick the blocks per workgroup of each level by timing `steps` steps per
  * trial (1, 2, 3, 4, 6, 8; finest level first, one level at a time) and keep the
  * fastest; if cache_path is non-NULL the choice is read from / written to
- * that JSON file keyed by the storage and the block counts.  The simulation
- * state is restored afterwards. */
+ * that JSON file keyed by the storage and the block counts.  Trials run one
+ * step per launch, the form the choice applies to.  The simulation state is
+ * restored afterwards. */
 sbt_status sbt_autotune(sbt_ctx *ctx, int32_t steps, const char *cache_path);
 /* Run n steps eagerly with HIP events around every launch, on the context's
  * stream.  out[0] = total ms of level (collide+stream) kernels, out[1] = their
@@ -352,7 +355,8 @@ sbt_status sbt_autotune(sbt_ctx *ctx, int32_t steps, const char *cache_path);
  * blocks and halo bands; substeps that do not depend on each other share a
  * launch), out[7] = its launch count, out[8] = its algorithmic bytes.
  * Forcing loops, which otherwise may share a launch with the level substeps
- * that follow them, run in launches of their own here. */
+ * that follow them, run in launches of their own here, and so does each step
+ * of a level whose steps otherwise share one. */
 sbt_status sbt_profile(sbt_ctx *ctx, int32_t n, double out[9]);
 /* Cell updates performed per sbt_step, summed over cases and levels. */
 sbt_status sbt_updates_per_step(sbt_ctx *ctx, int64_t *updates);

@@ -319,6 +319,7 @@ struct sbt_ctx {
   int static_dev = -1;             // device whose static array holds the memory (sbt_create_static), or -1
   // profiling
   bool profiling = false;
+  bool tuning = false;             // sbt_autotune: every step a launch of its own, whose shape the trials differ in
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_level, ev_fast, ev_mdf;
   double prof_bytes = 0.0, prof_updates = 0.0;
 };
@@ -1683,7 +1684,7 @@ sbt_status sbt_step(sbt_ctx *ctx, int32_t n) {
     sbt_status st = ensure_plans(X, X.stream);
     if (st) return st;
   }
-  const int ns = X.persistent || X.profiling ? 0 : steps_per_launch(X);
+  const int ns = X.persistent || X.profiling || X.tuning ? 0 : steps_per_launch(X);
   for (int t = 0; t < n;) {
     // the last launch of a call runs one step: the readouts stream from the
     // lattice it read
@@ -2153,6 +2154,7 @@ sbt_status sbt_autotune(sbt_ctx *ctx, int32_t steps, const char *cache_path) {
     return sbt_write_state(ctx, saved.data(), sb);
   };
   float best_ms = 0;
+  X.tuning = true;
   st = trial(cur, best_ms);
   for (int v = X.V - 1; v >= 0 && !st; --v) {
     for (int k : {1, 2, 3, 4, 6, 8}) {
@@ -2170,6 +2172,7 @@ sbt_status sbt_autotune(sbt_ctx *ctx, int32_t steps, const char *cache_path) {
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  X.tuning = false;
   X.kpw_level = cur;
   destroy_graphs(X);
   if (st) return st;

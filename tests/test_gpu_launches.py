@@ -311,3 +311,26 @@ def test_contexts_on_two_streams(env):
     for g, ref in zip(both, refs):
         g.synchronize()
         assert np.array_equal(g.read_state(), ref.read_state())
+
+
+def test_autotune_times_the_launches_it_chooses_for(env, tmp_path):
+    """Its trials run one step per launch, also on a level where a long call
+    runs several: only then do the candidates differ."""
+    import torch
+    P, O = env
+    g = P.Sim(W.tgv(64), "f32")
+    print("tgv64", flush=True)
+
+    def kernels(f):
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+            f()
+            g.synchronize()
+        return " ".join(e.name for e in prof.events())
+
+    names = kernels(lambda: g.step(24))
+    assert "multi_step_kernel" in names
+    before = g.read_state()
+    names = kernels(lambda: g.autotune(steps=24, cache_path=str(tmp_path / "tune.json")))
+    assert "level_tile_kernel" in names and "multi_step_kernel" not in names
+    assert np.array_equal(g.read_state(), before)
+    assert "multi_step_kernel" in kernels(lambda: g.step(24))
