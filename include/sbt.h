@@ -318,7 +318,8 @@ sbt_status sbt_write_state(sbt_ctx *ctx, const void *host, size_t bytes);
  *   computes block j); 0 (default) = automatic per launch size.  Launches of
  *   several steps (calls of more than 4 steps on a single periodic level
  *   without bodies and solid cells) take one block per workgroup always.
- * SBT_OPT_XCD_REMAP (default 1): map consecutive Morton blocks to one XCD.
+ * SBT_OPT_XCD_REMAP (default 1): map consecutive Morton blocks to one XCD
+ *   (launches of several steps always do).
  * SBT_OPT_PERSISTENT (default 0): run each step as one persistent launch
  *   (plan builder, forcing loops and level substeps as phases separated by
  *   grid barriers, every level block through the generic per-cell path)
