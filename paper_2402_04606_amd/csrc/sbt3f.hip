@@ -1375,8 +1375,7 @@ sbt_status sbt3f_create(const sbt3f_desc *desc, void *device_buf, size_t bytes, 
   }
   if (hipMemsetAsync(X->d_err, 0, 4, X->stream) != hipSuccess || hipStreamSynchronize(X->stream) != hipSuccess)
     return cleanup(fail3(SBT_ERR_DEVICE, "error flag reset failed"));
-  rec3(1, X->fo.m, X->phases);
-  if (X->fo.m == 1) X->phases.clear();
+  if (X->fo.m > 1) rec3(1, X->fo.m, X->phases);
   X->phases.push_back({0, 1});
   *out = X;
   return SBT_OK;

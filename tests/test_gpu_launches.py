@@ -334,3 +334,18 @@ def test_autotune_times_the_launches_it_chooses_for(env, tmp_path):
     assert "level_tile_kernel" in names and "multi_step_kernel" not in names
     assert np.array_equal(g.read_state(), before)
     assert "multi_step_kernel" in kernels(lambda: g.step(24))
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s", "bf16s"])
+@pytest.mark.parametrize("lattice", [19, 27])
+def test_one_level_forest_matches_oracle(env, storage, lattice):
+    """A forest without refinement is a schedule of one launch a step."""
+    from test_gpu_forest3d import _compare
+    P, O = env
+    wl = W.vortex3f(n0=32, m=1, boxes=(), lattice=lattice).replace(nx0=32, ny0=48, nz0=40)
+    print(storage, lattice, flush=True)
+    g, o = P.Sim3F(wl, storage), O.Oracle3FSim(wl)
+    g.step(6)
+    g.synchronize()
+    o.step(6)
+    _compare(g, o, wl, storage)
