@@ -349,3 +349,28 @@ def test_one_level_forest_matches_oracle(env, storage, lattice):
     g.synchronize()
     o.step(6)
     _compare(g, o, wl, storage)
+
+
+@pytest.mark.parametrize("size,box", [
+    ((136, 128, 72), (0, 0, 0, 136, 128, 72)),     # whole planes
+    ((136, 128, 72), (3, 5, 6, 131, 121, 65)),     # off the block faces
+    ((400, 384, 24), (1, 0, 5, 399, 384, 19)),     # whole planes, fewer than a block's
+    ((528, 256, 24), (1, 0, 4, 527, 255, 19)),     # rows of eight planes
+    ((528, 256, 24), (0, 3, 7, 528, 250, 5)),      # fewer planes than a block
+    ((16392, 8, 16), (5, 1, 3, 16387, 7, 12)),     # cells of eight rows
+], ids=str)
+def test_boxes_larger_than_the_staging_area(env, size, box):
+    """A readout cut into parts against readouts that fit in one."""
+    P, O = env
+    wl = W.vortex3f(n0=32, m=1, boxes=()).replace(nx0=size[0], ny0=size[1], nz0=size[2])
+    print(size, box, flush=True)
+    g = P.Sim3F(wl, "f32")
+    g.step(2)
+    whole = g.fields(0, box)
+    x0, y0, z0, nx, ny, nz = box
+    for z in range(0, nz, 3):
+        for x in range(0, nx, 2999):
+            dx, dz = min(2999, nx - x), min(3, nz - z)
+            part = g.fields(0, (x0 + x, y0, z0 + z, dx, ny, dz))
+            for a, b in zip(whole, part):
+                assert np.isfinite(b).all() and np.array_equal(a[z:z + dz, :, x:x + dx], b), (x, z)
