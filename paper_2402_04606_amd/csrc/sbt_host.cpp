@@ -257,6 +257,7 @@ struct CaseHost {
   std::vector<std::vector<uint8_t>> smask;  // per level: dense solid mask (empty = none)
   std::vector<std::vector<double>> sq;      // per level: dense [cell][9] wall fractions
   int n_markers = 0;
+  double arc = 0.0;                // sum of the markers' ds
   int win_cap = 0;
   size_t hist_cap = 0;
 };
@@ -302,6 +303,7 @@ struct sbt_ctx {
   int cell_cap = 0;             // stencil cells per IBM plan (fits the forcing kernel's LDS)
   int plan_bufs = 1;            // IBM plan buffers per body: the finest substeps of a step
   int max_body_markers = 0;     // largest body set so far (LDS table stride)
+  double max_body_arc = 0.0;    // longest marker arc (sum of ds) of a body
   int n_cu = 0;                 // compute units of the device (once a body is set)
   int64_t k_host = 0;           // finest substeps issued (every body's forcing-loop counter)
   // IBM plans beside the forcing loops: every plan_chunk-th loop's launch
@@ -902,16 +904,26 @@ IbmArgs beside_args(const sbt_ctx &X) {
 // (the loop's registers and LDS), which costs more than it saves where the
 // blocks are many, sooner with 2-byte storage, which has fewer bytes in
 // flight per wavefront.  Measured, us a step apart / shared: a cylinder of
-// 126 markers on 512 blocks F64 19.7 / 17.1, F32 17.7 / 13.8, F16S 17.5 /
-// 13.9; on 2048 28.0 / 24.7, 20.9 / 16.4, 18.3 / 15.0; on 4608 42.1 / 40.1,
-// 28.0 / 21.8, 22.8 / 21.4; on 8192 68.5 / 71.3, 36.9 / 33.8, 28.0 / 32.8; on
-// 18432 144 / 151, 77.5 / 84.5, 40.6 / 63.0.  At most 16 bodies: their loops
-// take half of XCD 0's CUs; and the device must be all 8 XCDs (see
-// mdf_level_kernel).  At most 256 markers: the shared kernel's loop spills 9
-// registers, which costs a long one more than the launch saved (200 markers, 8
-// loops a step, 137 apart and 130 shared; 402 markers, 4 loops, 114 and 121).
+// 126 markers on 512 blocks F64 19.0 / 18.6, F32 17.3 / 15.7, F16S 17.3 /
+// 15.7; on 2048 27.7 / 24.1, 20.9 / 17.2, 18.2 / 16.6; on 4608 41.6 / 39.6,
+// 27.7 / 22.5, 22.8 / 21.9; on 6144 50.5 / 49.1, 31.3 / 27.1, 25.2 / 26.1; on
+// 6656 52.5 / 53.2, 32.8 / 28.6, 25.8 / 27.7; on 8192 68.2 / 71.4, 36.7 / 34.4,
+// 28.3 / 32.9; on 18432 143 / 151, 78.2 / 84.6, 41.3 / 63.6.
+// At most 16 bodies, each of which takes a CU from the collisions for as long
+// as its loop runs (F32, n rings of 60 markers on 64 blocks each: 16 17.4 /
+// 14.1, 24 19.0 / 18.4, 32 21.8 / 22.9; n small wings on 3 levels: 16 72.9 /
+// 61.8, 24 79.9 / 72.5, 32 86.2 / 88.0).  At most 256 cells of marker arc, four
+// times which is about the body's stencil cells: past 1024 lanes own second
+// cells, whose weights the loop looks up, and the shared kernel's, which spills
+// 4 registers (8 in F64), is then slower (F32, a fixed circle on 3 levels, 4
+// loops a step: arc 200 72.8 / 70.1, 256 82.2 / 82.4, 300 90.1 / 90.8, 402
+// 111 / 117; a wing of arc 131 on 4 levels, 8 loops: 200 markers 138 / 124,
+// 300 185 / 169, 402 221 / 206; 9 cases of up to 300 markers BF16S 198 / 183).
+// At most 512 markers (two lanes each), and a whole device of 256 CUs, on
+// which all of this was measured.
 bool forcing_shares(const sbt_ctx &X, const Phase *ph, int n) {
-  if (X.n_bodies == 0 || X.n_bodies > 16 || X.n_cu != 256 || X.profiling || X.max_body_markers > kMaxMarkers / 4) return false;
+  if (X.n_bodies == 0 || X.n_bodies > 16 || X.n_cu != 256 || X.profiling) return false;
+  if (X.max_body_markers > kMaxMarkers / 2 || !(X.max_body_arc <= 256.0)) return false;
   int64_t items = 0;
   for (int i = 0; i < n; ++i) {
     const Pool &P = X.pools[ph[i].v];
@@ -919,7 +931,7 @@ bool forcing_shares(const sbt_ctx &X, const Phase *ph, int n) {
     if (!P.solid.empty() || kpw > 1) return false;
     items += (int64_t)(P.fast.size() + P.slow.size()) + (ph[i].p == 1 ? ((int64_t)P.band.size() + 255) / 256 : 0);
   }
-  return items <= (X.storage == SBT_F64 ? 6656 : (X.storage == SBT_F32 ? 8192 : 4096));
+  return items <= (X.storage == SBT_F64 ? 6144 : (X.storage == SBT_F32 ? 8192 : 4096));
 }
 
 // One launch of the forcing loops and the level substeps ph[0 .. n).
@@ -1625,6 +1637,10 @@ sbt_status sbt_set_body(sbt_ctx *ctx, int32_t c, const sbt_body *body) {
   C.dev.n_markers = body->n;
   std::memcpy(C.dev.bp, body->p, sizeof(body->p));
   C.n_markers = body->n;
+  C.arc = 0.0;
+  for (int j = 0; j < body->n; ++j) C.arc += std::fabs(body->ds[j]);
+  X.max_body_arc = 0.0;
+  for (const CaseHost &K : X.cs) X.max_body_arc = std::max(X.max_body_arc, K.arc);
   HIPCHK(hipMemcpy(X.d_cases + c, &C.dev, sizeof(CaseDev), hipMemcpyHostToDevice));
   // the bodies in case order, one forcing workgroup each
   std::vector<CaseDev> bd;

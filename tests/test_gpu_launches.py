@@ -374,3 +374,19 @@ def test_boxes_larger_than_the_staging_area(env, size, box):
             part = g.fields(0, (x0 + x, y0, z0 + z, dx, ny, dz))
             for a, b in zip(whole, part):
                 assert np.isfinite(b).all() and np.array_equal(a[z:z + dz, :, x:x + dx], b), (x, z)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f16s"])
+@pytest.mark.parametrize("wl", [ring(512, 40.0), ring(256, 40.0), W.flapping_ellipse(n_markers=402)],
+                         ids=["ring512", "ring256", "wing402"])
+def test_long_forcing_loops_that_share_a_launch(env, wl, storage):
+    """Bodies of up to 512 markers on an arc of at most 256 cells, the largest
+    that share a launch, against launches of their own."""
+    P, O = env
+    print(wl.name, storage, flush=True)
+    apart, shared = P.Sim(wl, storage, history_cap=1), P.Sim(wl, storage, history_cap=1)
+    for n in (1, 4):
+        apart.profile(n)
+        shared.step(n)
+        shared.synchronize()
+        assert np.array_equal(apart.read_state(), shared.read_state()), n
