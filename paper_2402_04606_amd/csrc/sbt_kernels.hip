@@ -2468,9 +2468,10 @@ __device__ __forceinline__ void mdf_body(const MdfArgs a, unsigned body) {
 #ifndef SBT_PERSISTENT_TU
 // Workgroups [0, n_bodies) run the forcing loops; the rest, on CUs the loops
 // leave idle, build plans of later substeps into buffers whose collisions
-// are done.  One body of 200 markers: 11.9 us, 12.5 with plans beside it
-// (12.6 before, and 16.3 a step for the plans' own launch); 402 fixed ones
-// 21.2 us (21.7, and 33.9 a step); 64 bodies 18.4 us (16.4, and 29.3).
+// are done.  One body of 200 markers: 11.1 us, 12.5 with plans beside it
+// (12.6 when the plans had a launch of their own, 16.3 a step); 402 fixed ones
+// 20.5 us (21.7, and 33.9 a step); 64 bodies 16.9 us, 19.0 with plans beside
+// them (16.4, and 29.3 a step).
 template <int ST, bool PAIR>
 __global__ __launch_bounds__(MDF_THREADS) void mdf_kernel(MdfArgs a, IbmArgs p, int n_bodies) {
   if ((int)blockIdx.x >= n_bodies) prep_item<16 + ST * 2 + PAIR, PAIR>(p, blockIdx.x - n_bodies);
@@ -2495,9 +2496,10 @@ __global__ __launch_bounds__(MDF_THREADS) void mdf_kernel(MdfArgs a, IbmArgs p, 
 // anything.
 // The loop's latency bounds it, then what follows the wait: the force density
 // goes to where every XCD reads it, and the collision of blocks already in
-// LDS.  A wing of 200 markers on 4 levels takes 130 us a step (8 such
-// launches) where forcing loops and levels apart took 137, a fixed cylinder of
-// 126 markers on 1024 x 512 cells 24.7 where they took 28.1 (F64).
+// LDS.  A wing of 200 markers on 4 levels takes 124 us a step (8 such
+// launches of 15 to 16 us) where forcing loops and levels apart take 138, a
+// fixed cylinder of 126 markers on 1024 x 512 cells 24.1 where they take 27.7
+// (F64).
 template <int ST>
 __global__ __launch_bounds__(MDF_THREADS) void mdf_level_kernel(TileArgs, const CaseDev *__restrict__ cases, MdfArgs m, IbmArgs p,
                                                                int n_bodies, int n_head, int odd, uint32_t spins,
