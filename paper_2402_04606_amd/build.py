@@ -14,6 +14,11 @@ HIP_FLAGS = [
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
 ]
 
+# Host code aligned on its own account: with the defaults the same planner took
+# 5.2 to 6.9 ms for a wing on 4 levels, depending on the address the linker gave
+# it; so it takes 5.0 at every one (26.4 ms for 9 cases, 28 to 36 before).
+HOST_FLAGS = ["--offload-arch=gfx950", "-O3", "-falign-functions=64", "-falign-loops=32", "-std=c++17", "-fPIC", "-Wall"]
+
 
 def build(verbose=False, jobs=2):
     csrc = os.path.join(_HERE, "csrc")
@@ -27,8 +32,7 @@ def build(verbose=False, jobs=2):
         cmd = ["hipcc", *HIP_FLAGS, *inc, *lang, "-c", os.path.join(csrc, src), "-o", obj]
         if src.endswith(".cpp"):
             # host-only translation unit (uses the HIP runtime API)
-            cmd = ["hipcc", "--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-Wall", *inc, "-c",
-                   os.path.join(csrc, src), "-o", obj]
+            cmd = ["hipcc", *HOST_FLAGS, *inc, "-c", os.path.join(csrc, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append(subprocess.Popen(cmd))
