@@ -1257,7 +1257,7 @@ sbt_status capture_all(sbt_ctx &X) {
   for (int flip = 0; flip < 2; ++flip) {
     if (flip) {  // one step on
       X.pools[0].cur ^= 1;
-      X.k_host += forcing_phases(X);
+      if (X.n_bodies > 0) X.k_host += forcing_phases(X);
     }
     sbt_status st = SBT_OK;
     for (int si = 0; si < 3 && !st; ++si) {

@@ -390,3 +390,23 @@ def test_long_forcing_loops_that_share_a_launch(env, wl, storage):
         shared.step(n)
         shared.synchronize()
         assert np.array_equal(apart.read_state(), shared.read_state()), n
+
+
+@pytest.mark.parametrize("make", [lambda: W.tgv(64), lambda: nest(1, True), lambda: nest(3, False), lambda: ring(40, 8.0),
+                                  lambda: W.small_refined_flap(m=2)], ids=["plane", "walls", "nest", "ring", "flap"])
+def test_graphs_are_captured_at_the_first_step(env, make):
+    """All graphs that a run can reach: no later step captures one."""
+    import torch
+    P, O = env
+    wl = make()
+    print(wl.name, flush=True)
+    g = P.Sim(wl, "f32")
+
+    def captures(n):
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+            g.step(n)
+            g.synchronize()
+        return sum(e.name == "hipGraphInstantiate" for e in prof.events())
+
+    assert captures(1) == 6
+    assert [captures(n) for n in (1, 1, 3, 2, 4, 5, 1)] == [0] * 7
