@@ -1,5 +1,6 @@
 #include "host_copy.h"
 
+#include <stdlib.h>
 #include <string.h>
 
 #include <atomic>
@@ -10,6 +11,7 @@
 namespace sbt {
 
 HostCopy::~HostCopy() {
+  free(tmp_);
   for (hipEvent_t &e : ev_)
     if (e) (void)hipEventDestroy(e);
   if (pin_) (void)hipHostFree(pin_);
@@ -32,7 +34,25 @@ bool HostCopy::ready() {
 
 hipError_t HostCopy::to_host(const Piece *p, int n, hipStream_t s) {
   size_t total = 0;
-  for (int i = 0; i < n; ++i) total += p[i].bytes;
+  bool joined = n > 1;  // the pieces follow one another on the device
+  for (int i = 0; i < n; ++i) {
+    joined = joined && (i == 0 || p[i].dev == static_cast<const char *>(p[i - 1].dev) + p[i - 1].bytes);
+    total += p[i].bytes;
+  }
+  if (joined && total <= kSmall) {  // one transfer, then a copy per piece
+    char *buf = pin_;
+    if (!buf) {
+      if (!tmp_) tmp_ = static_cast<char *>(malloc(kSmall));
+      buf = tmp_;
+    }
+    if (buf) {
+      hipError_t e = hipMemcpyAsync(buf, p[0].dev, total, hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+      if (e != hipSuccess) return e;
+      for (int i = 0; i < n; buf += p[i++].bytes) memcpy(p[i].host, buf, p[i].bytes);
+      return hipSuccess;
+    }
+  }
   int dev = 0;
   // the per-thread stream is another one in each worker, which would not wait
   // for what the caller's holds: the caller copies by itself

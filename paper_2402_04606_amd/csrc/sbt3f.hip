@@ -1042,6 +1042,9 @@ void build_tables(const Forest &Fo, int l, std::vector<Blk3> &meta, std::vector<
 size_t stor_bytes3(int st) { return st == 0 ? 8 : (st == 1 ? 4 : 2); }
 size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 constexpr int kStageBlocks = 2048;
+// Cells of a readout up to which NaN around the owned part is written by the
+// host instead of copied.
+constexpr int64_t kSparseCells = (int64_t)1 << 19;
 
 struct Pool3 {
   int n_own = 0, n_halo = 0, code_rows = 0;
@@ -1502,6 +1505,39 @@ sbt_status sbt3f_read_box(sbt3f_ctx *ctx, int32_t level, const int32_t box[6], d
   };
   std::vector<int32_t> blocks = blocks_in_box(X, level, box);
   const LevelHost &H = X.fo.L[level];
+  // a small box that the level owns little of: the part that its blocks span
+  const int64_t all = plane * box[5];
+  if (all <= kSparseCells) {
+    int lo[3] = {box[3], box[4], box[5]}, hi[3] = {0, 0, 0};
+    for (int32_t b : blocks) {
+      int o[3];
+      H.unkey(H.own_keys[b], o[0], o[1], o[2]);
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = std::min(lo[a], std::max(o[a] * kB3 - box[a], 0));
+        hi[a] = std::max(hi[a], std::min((o[a] + 1) * kB3 - box[a], box[3 + a]));
+      }
+    }
+    const int64_t n = blocks.empty() ? 0 : (int64_t)(hi[0] - lo[0]) * (hi[1] - lo[1]) * (hi[2] - lo[2]);
+    if (2 * n <= all && n <= cap && (int)blocks.size() <= sb) {
+      double *dst[4] = {rho, ux, uy, uz};
+      for (double *f : dst) std::fill(f, f + all, __builtin_nan(""));
+      if (n == 0) return SBT_OK;
+      const int32_t part[6] = {box[0] + lo[0], box[1] + lo[1], box[2] + lo[2], hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]};
+      std::vector<double> tmp(4 * (size_t)n);
+      HIPCHK3(sbt_launch_fill_nan(X.d_stage, 4 * (size_t)n, SBT_F64, X.stream));
+      HIPCHK3(hipMemcpyAsync(X.d_stage_list, blocks.data(), blocks.size() * 4, hipMemcpyHostToDevice, X.stream));
+      st = launch_level3(X, level, X.d_stage_list, (int)blocks.size(), M3_READOUT | (X.post ? 0 : M3_LOCAL), false, part);
+      if (st) return st;
+      const sbt::HostCopy::Piece all4 = {X.d_stage, tmp.data(), tmp.size() * sizeof(double)};
+      HIPCHK3(X.copy.to_host(&all4, 1, X.stream));
+      const double *from = tmp.data();
+      for (double *f : dst)
+        for (int z = lo[2]; z < hi[2]; ++z)
+          for (int y = lo[1]; y < hi[1]; ++y, from += part[3])
+            std::copy(from, from + part[3], f + (size_t)z * plane + (size_t)y * row + lo[0]);
+      return SBT_OK;
+    }
+  }
   const int bz0 = box[2] / kB3;
   std::vector<std::vector<int32_t>> layer;  // of several parts: the box's blocks by block plane
   if (plane * box[5] > cap) {

@@ -410,3 +410,24 @@ def test_graphs_are_captured_at_the_first_step(env, make):
 
     assert captures(1) == 6
     assert [captures(n) for n in (1, 1, 3, 2, 4, 5, 1)] == [0] * 7
+
+
+@pytest.mark.parametrize("n0,boxes", [(32, ((1, 2, 2, 2, 6, 6, 6),)),               # level 1 of 2^18 cells, an eighth owned
+                                      (40, ((1, 1, 1, 1, 5, 9, 9),)),               # 512000 cells, a third
+                                      (48, ((1, 2, 2, 2, 6, 6, 6),))], ids=str)     # more than 2^19 cells
+def test_readouts_of_a_level_owned_in_part(env, n0, boxes):
+    """Boxes with NaN around and inside the owned cells, in and out of the part
+    that the level's blocks span, against the oracle."""
+    P, O = env
+    wl = W.vortex3f(n0=n0, boxes=boxes)
+    print(n0, boxes, flush=True)
+    g, o = P.Sim3F(wl, "f64"), O.Oracle3FSim(wl)
+    g.step(2)
+    o.step(2)
+    n = 2 * n0
+    for l, box in ((1, (0, 0, 0, n, n, n)), (1, (5, 3, 7, n - 6, n - 9, n - 11)), (1, (0, 0, 0, 7, 6, 5)),
+                   (1, (n - 20, 0, 0, 20, n, n)), (1, (17, 18, 19, 9, 3, 20)), (0, (0, 0, 0, n0, n0, n0)), (0, (9, 9, 9, 6, 5, 4))):
+        want = o.fields(l)
+        x, y, z, nx, ny, nz = box
+        for a, b in zip(g.fields(l, box), want):
+            assert np.array_equal(a, b[z:z + nz, y:y + ny, x:x + nx], equal_nan=True), (l, box)

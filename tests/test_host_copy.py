@@ -56,15 +56,21 @@ PROGRAM = r"""
 int main(int argc, char **argv) {
   hipStream_t s = (hipStream_t)strtoul(argv[1], nullptr, 0);
   const size_t sizes[3] = {strtoul(argv[2], nullptr, 0), 1, 12345};
+  const size_t gap = strtoul(argv[3], nullptr, 0);  // between the pieces on the device
   sbt::HostCopy copy;
   for (int pass = 0; pass < 2; ++pass) {
-    std::vector<std::vector<char>> dev, host;
+    std::vector<char> dev(sizes[0] + sizes[1] + sizes[2] + 2 * gap);
+    std::vector<std::vector<char>> host, want;
     sbt::HostCopy::Piece pc[3];
-    for (size_t n : sizes) dev.emplace_back(n, 0), host.emplace_back(n, 1);
-    for (int i = 0; i < 3; ++i) pc[i] = {dev[i].data(), host[i].data(), sizes[i]};
-    push(s, [&] { for (auto &d : dev) for (size_t i = 0; i < d.size(); ++i) d[i] = (char)(i * 31 + 7 + pass); });
+    size_t at = 0;
+    for (size_t n : sizes) host.emplace_back(n, 1), want.emplace_back(n, 1);
+    for (int i = 0; i < 3; at += sizes[i++] + gap) {
+      pc[i] = {dev.data() + at, host[i].data(), sizes[i]};
+      for (size_t k = 0; k < sizes[i]; ++k) want[i][k] = (char)((at + k) * 31 + 7 + pass);
+    }
+    push(s, [&] { for (size_t i = 0; i < dev.size(); ++i) dev[i] = (char)(i * 31 + 7 + pass); });
     if (copy.to_host(pc, 3, s) != hipSuccess) return 2;
-    if (host != dev) { puts("copied before the kernel"); return 1; }
+    if (host != want) { puts("copied before the kernel"); return 1; }
   }
   return 0;
 }
@@ -83,10 +89,12 @@ def program(tmp_path_factory):
     return exe
 
 
+@pytest.mark.parametrize("gap", [0, 8])
 @pytest.mark.parametrize("nbytes", [1000, (4 << 20) + 5, 11 << 20])
 @pytest.mark.parametrize("stream", ["0", "2", "0x1000"], ids=["default", "per_thread", "own"])
-def test_copies_follow_the_callers_stream(program, stream, nbytes):
+def test_copies_follow_the_callers_stream(program, stream, nbytes, gap):
     """The default stream, the per-thread stream and one of the program's own,
-    below and above the size from which several threads copy."""
-    r = subprocess.run([program, stream, str(nbytes)], capture_output=True, text=True, timeout=60)
+    below and above the size from which several threads copy, pieces that lie
+    together on the device and apart."""
+    r = subprocess.run([program, stream, str(nbytes), str(gap)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
